@@ -117,7 +117,7 @@ def _head(case, g, H):
     V, d = case["V"], case["d"]
     W = torch.randn(V, d, generator=g, device=DEV).mul_(0.02)
     rows = H.shape[0]
-    target = torch.randint(0, V, (rows,), generator=g, device=DEV)
+    target = torch.randperm(V, generator=g, device=DEV)[:rows]     # distinct: one row adds to a token
     Hf = H.float()
     boost = Hf * (0.12 * (4096 / d) ** 0.5 / Hf.norm(dim=1, keepdim=True))
     boost[torch.rand(rows, generator=g, device=DEV) < FLAT] = 0
