@@ -46,6 +46,8 @@ struct TileCfg {
   // loop: the whole tile of logits waits in its own buffer, [TV][BR][EPI_V]
   // fp32, while the copies of the next tile stream.
   static constexpr bool DEFER = BR <= 32;
+  // MFMA-bound tiles: the two waves of a SIMD alternate (see the kernel).
+  static constexpr bool PINGPONG = WAVES_R == 2 && STAGES == 2 && BK == 64;
   // There the top-K runs on wavefronts of its own (SPLIT_): NCW consumer
   // waves own the key lists and fold the staged tile while the NW compute
   // waves issue the next tile's copies and products, one of each per SIMD.
@@ -54,7 +56,9 @@ struct TileCfg {
   // all; NC own lists.
   static constexpr int NCW = DEFER && SPLIT_ ? NW : 0;
   static constexpr int NTA = 64 * (NW + NCW);
-  static constexpr int NC = NCW ? 64 * NCW : NT;
+  // On the 8-wave tiles two threads own lists per position (the first 2 * BR
+  // threads of the workgroup).
+  static constexpr int NC = NCW ? 64 * NCW : (WAVES_R == 2 ? 2 * BR : NT);
   static constexpr int WV = BV / WAVES_V, WR = BR / WAVES_R, TV = WV / 16, TR = WR / 16;
   static constexpr int CPR = BK / 8;            // 16-byte chunks per staged row
   static constexpr int RPI = 64 / CPR;          // staged rows one DMA instruction fills
@@ -77,7 +81,7 @@ struct TileCfg {
   // Filtered epilogue: the list of the second thread of every position as
   // floats, [BR][16], read by the first to bound the position's KP-th key.
   static constexpr int U_OFF = POS_OFF + BR * 8 + 16;
-  static constexpr int U_BYTES = BR >= 128 ? BR * 16 * 4 : 0;
+  static constexpr int U_BYTES = WAVES_R == 2 ? BR * 16 * 4 : 0;
   static constexpr int LDS_BYTES = U_OFF + U_BYTES;
   // Sampling pass: each thread keeps up to CKR candidate ids of its row in
   // registers, so testing a token against them touches no memory (a global
@@ -86,10 +90,11 @@ struct TileCfg {
   static constexpr int CKR = BR <= 64 ? 16 : 8;
   // survivors a position's queue holds per tile (the queues use the stage
   // buffer the epilogue aliases)
-  static constexpr int QCAP = STAGE_BYTES / (BR * 8);
+  static constexpr int QCAP = 32;
+  static_assert(WAVES_R < 2 || BR * QCAP * 8 <= STAGE_BYTES, "survivor queues");
   static_assert(ROWS % (RPI * NW) == 0 && BV % RPI == 0, "DMA instructions must tile the stage");
   static_assert(WV % 16 == 0 && WR % 16 == 0, "wave tile must be a multiple of 16");
-  static_assert(NT % BR == 0 && (TPP & (TPP - 1)) == 0, "epilogue thread mapping");
+  static_assert(NC % BR == 0 && NC <= NTA && (TPP & (TPP - 1)) == 0, "epilogue thread mapping");
   static_assert(BK % 32 == 0 && (CPR == 4 || CPR == 8 || CPR == 16 || CPR == 32), "reduction slice");
   static_assert(EPI_V % (4 * TPP) == 0 && EPI_V >= 32, "epilogue chunking");
   static_assert(!DEFER || TPP % 4 == 0, "row floors of the deferred fold are read as float4");
@@ -160,10 +165,13 @@ __device__ __forceinline__ void tile_of(int logical, int nblocks, int n_rtiles, 
   }
 }
 
-// Equal vocabulary shares for weight-streaming shapes, and list floors shared
-// among the epilogue threads of a row (both described where they are used).
-constexpr bool kEvenShares = true;
+// List floors shared among the epilogue threads of a row (described where it
+// is used).
 constexpr bool kRowThreshold = true;  // where TPP <= 2, and in the deferred fold
+
+// Longest lists of the filtered epilogue (see the kernel); longer ones fold
+// every logit from staged copies.
+constexpr int kFiltKeys = 16;
 
 // Whether the per-position lists fit in LDS for the in-workgroup merge (the
 // stage buffers are idle by then).
@@ -277,7 +285,7 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
   // position's list owners then fold.  A tile whose queues overflow, and a
   // first tile that is not whole, take the full path.  Lists of up to 16
   // keys; longer lists keep the full path on every tile.
-  constexpr bool kFilt = !SAMPLE && C::BR >= 128 && C::EPI_ALIAS && KP <= 16;
+  constexpr bool kFilt = !SAMPLE && C::WAVES_R == 2 && C::EPI_ALIAS && KP <= kFiltKeys;
   constexpr bool kSeed = kFilt;
   float* const s_pthr = reinterpret_cast<float*>(smem + C::POS_OFF);        // [BR]
   int* const s_cnt = reinterpret_cast<int*>(smem + C::POS_OFF + C::BR * 4);  // [BR]
@@ -366,7 +374,7 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
 
   // roles (see TileCfg::NCW); without consumer waves every wave does both
   const bool computer = C::NCW == 0 || wave < C::NW;
-  const bool consumer = C::NCW == 0 || wave >= C::NW;
+  const bool consumer = C::NCW ? wave >= C::NW : (C::NC == C::NTA || tid < C::NC);
   const int ctid = C::NCW ? (consumer ? tid - C::NT : 0) : tid;  // index among the list owners
   const int ep = ctid % C::BR, esub = ctid / C::BR;
   uint64_t list[KP];
@@ -513,18 +521,81 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
   }
 
   floatx4 acc[C::TV][C::TR];
-#pragma unroll
-  for (int a = 0; a < C::TV; ++a)
-#pragma unroll
-    for (int b = 0; b < C::TR; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  if (computer) {
+  // wait for this thread's LDS operations, or for all of its copies
+  auto lds_wait = [] { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8)); };
+  auto vm_wait = [] { __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8)); };
+  auto phase_end = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto read_frags = [&](const unsigned char* sb, int kk, bf16x8 (&a)[C::TV], bf16x8 (&b)[C::TR]) {
 #pragma unroll
-    for (int st = 0; st < C::STAGES - 1; ++st) issue(st);
-  }
+    for (int y = 0; y < C::TR; ++y)
+      b[y] = *reinterpret_cast<const bf16x8*>(sb + (C::BV + wr * C::WR + y * 16) * C::CPR * 16 + lane_off[kk]);
+#pragma unroll
+    for (int x = 0; x < C::TV; ++x)
+      a[x] = *reinterpret_cast<const bf16x8*>(sb + (wv * C::WV + x * 16) * C::CPR * 16 + lane_off[kk]);
+  };
+  auto products = [&](const bf16x8 (&a)[C::TV], const bf16x8 (&b)[C::TR]) {
+#pragma unroll
+    for (int x = 0; x < C::TV; ++x)
+#pragma unroll
+      for (int y = 0; y < C::TR; ++y)
+        acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], b[y], acc[x][y], 0, 0, 0);
+  };
 
-  for (int tl = 0; tl < n_tiles; ++tl) {
-    for (int kt = 0; kt < nk; ++kt) {
+  // The reduction slices of tile tl.  (Skipping the products of 16-row blocks
+  // past the end of a share's last tile gained nothing: a slice takes the time
+  // of its copies.)  The accumulators start at zero here, not after the
+  // epilogue: carried from tile to tile they would cross both loops below.
+  auto slices = [&](int tl) {
+#pragma unroll
+    for (int a = 0; a < C::TV; ++a)
+#pragma unroll
+      for (int b = 0; b < C::TR; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    int kt0 = 0;
+    if constexpr (C::PINGPONG) {
+      // The two waves of a SIMD (w and w + 4: wr = 0 and 1) take turns: while
+      // one runs the 32 products of a 32-wide step, the other reads its next
+      // operands from LDS and issues its copies, with a barrier after each
+      // phase.  The second group starts one phase late and the first waits
+      // one out at the end, so both pass the same barriers.  In lockstep both
+      // waves of a SIMD wait on LDS together and then contend for the matrix
+      // cores: 3347 against 3240 us at 4096 rows x 126464 tokens (d = 4096),
+      // 500 against 476 us at 512.  Raising the priority of the multiplying
+      // wave made no difference, nor did spreading the copies over the phases.
+      //
+      // Phase p of slice g is 4g + p, one more for the second group.  Its
+      // first phase refills the buffer of slice g - 1, which the other group
+      // finished reading in phase 4g - 1 at the latest; both groups' copies
+      // have landed by the end of phase 4g + 3, before slice g + 1 is read.
+      // The last slice of a ragged d, which needs zeroing, runs in the plain
+      // loop below.
+      kt0 = tail ? nk - 1 : nk;
+      stage_sync<0>();
+      if (wr == 1) phase_end();
+      for (int kt = 0; kt < kt0; ++kt) {
+        const int g = tl * nk + kt;
+        const unsigned char* sb = smem + (g % C::STAGES) * C::STAGE_BYTES;
+        bf16x8 b[C::TR], a[C::TV];
+        issue(g + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          read_frags(sb, kk, a, b);
+          if (kk == 1 && wr == 1) vm_wait();
+          lds_wait();
+          phase_end();
+          products(a, b);
+          if (kk == 1 && wr == 0) vm_wait();
+          phase_end();
+        }
+      }
+      if (wr == 0) phase_end();
+    }
+    for (int kt = kt0; kt < nk; ++kt) {
       const int g = tl * nk + kt;
       // slice g landed; everyone is done with slice g-1 (in the last slices
       // fewer younger copies exist, so wait for all)
@@ -544,36 +615,36 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
       }
       if (computer) {
 #pragma unroll
-      for (int kk = 0; kk < C::BK / 32; ++kk) {
-        // all operand fragments of this 32-wide slice first, then the MFMAs,
-        // so LDS latency overlaps the first products instead of every row
-        bf16x8 b[C::TR], a[C::TV];
-#pragma unroll
-        for (int y = 0; y < C::TR; ++y)
-          b[y] = *reinterpret_cast<const bf16x8*>(sb + (C::BV + wr * C::WR + y * 16) * C::CPR * 16 + lane_off[kk]);
-#pragma unroll
-        for (int x = 0; x < C::TV; ++x)
-          a[x] = *reinterpret_cast<const bf16x8*>(sb + (wv * C::WV + x * 16) * C::CPR * 16 + lane_off[kk]);
-#pragma unroll
-        for (int x = 0; x < C::TV; ++x)
-#pragma unroll
-          for (int y = 0; y < C::TR; ++y)
-            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], b[y], acc[x][y], 0, 0, 0);
-        // keep that order: every fragment read issued before the products
-        __builtin_amdgcn_sched_group_barrier(0x100, C::TV + C::TR, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, C::TV * C::TR, 0);
-      }
+        for (int kk = 0; kk < C::BK / 32; ++kk) {
+          // all operand fragments of this 32-wide slice first, then the MFMAs,
+          // so LDS latency overlaps the first products instead of every row
+          bf16x8 b[C::TR], a[C::TV];
+          read_frags(sb, kk, a, b);
+          products(a, b);
+          // keep that order: every fragment read issued before the products
+          __builtin_amdgcn_sched_group_barrier(0x100, C::TV + C::TR, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, C::TV * C::TR, 0);
+        }
       }
       if constexpr (C::DEFER) {
         // the previous tile's top-K, spread evenly over this tile's slices
         while (pend < kItems && kt * kItems >= pend * nk) consume_item(pend++);
       }
     }
+  };
+
+  if (computer) {
+#pragma unroll
+    for (int st = 0; st < C::STAGES - 1; ++st) issue(st);
+  }
+
+  for (int tl = 0; tl < n_tiles; ++tl) {
+    const int v0 = tile_start(tl), vend = tile_end(tl);
+    slices(tl);
 
     // Fused top-K over this tile.  Chunk x stages accumulator block x of
     // every wave as fp32 [position][wave_v * 16 + column]; each thread then
     // folds its position's columns into its running list.
-    const int v0 = tile_start(tl), vend = tile_end(tl);
     if constexpr (C::DEFER) {
       while (pend < kItems) consume_item(pend++);  // tiles shorter than kItems slices
       lds_sync();  // every thread has finished with the previous tile's logits
@@ -585,7 +656,6 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
             const int p = wr * C::WR + y * 16 + l15;
             *reinterpret_cast<floatx4*>(sD + (x * C::BR + p) * C::EPI_V + epi_slot(p, wv * 4 + (lane >> 4)) * 4) =
                 acc[x][y];
-            acc[x][y] = floatx4{0.f, 0.f, 0.f, 0.f};
           }
         }
       }
@@ -610,8 +680,10 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
     }
     if constexpr (kFilt) {
       const bool whole = vend - v0 == C::BV;
-      // seed the first two tiles; after them the two lists bound tightly
-      const bool seed = kSeed && whole && tl < 2;
+      // seed the first two tiles; after them the two lists bound tightly (a
+      // partial second tile too: the first has left a finite bound, so the
+      // rows masked below never pass)
+      const bool seed = kSeed && (tl == 0 ? whole : tl == 1);
       if (tl > 0 || seed) {
         // lane l holds, for position wr*WR + y*16 + l%16, the logits of
         // vocabulary rows wv*WV + x*16 + 4*(l/16) + q of the tile
@@ -622,6 +694,16 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
         // queue are 256 bytes apart).
         static_assert((C::QCAP & (C::QCAP - 1)) == 0, "queue slots");
         auto qslot = [](int p, int i) { return p * C::QCAP + (i ^ (p & (C::QCAP - 1))); };
+        const int vl0 = v0 + wv * C::WV + 4 * (lane >> 4);
+        if (vend - v0 < C::BV) {  // the share's last tile: rows past its end never enter
+#pragma unroll
+          for (int x = 0; x < C::TV; ++x)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (vl0 + x * 16 + q >= vend)
+#pragma unroll
+                for (int y = 0; y < C::TR; ++y) acc[x][y][q] = -3.0e38f;
+        }
         if (seed) {
           // Seed from the tile itself: each of the 16 lanes that hold a
           // position's 256 logits offers its M largest, and the KP-th
@@ -672,16 +754,6 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
         float pt[C::TR];
 #pragma unroll
         for (int y = 0; y < C::TR; ++y) pt[y] = s_pthr[wr * C::WR + y * 16 + l15];
-        const int vl0 = v0 + wv * C::WV + 4 * (lane >> 4);
-        if (vend - v0 < C::BV) {  // the share's last tile: rows past its end never enter
-#pragma unroll
-          for (int x = 0; x < C::TV; ++x)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              if (vl0 + x * 16 + q >= vend)
-#pragma unroll
-                for (int y = 0; y < C::TR; ++y) acc[x][y][q] = -3.0e38f;
-        }
         // Per position of the lane, without branches: how many of its 16
         // logits reach the threshold, the last of them and the largest logit.
         // (Branching per block of logits made the whole wavefront walk every
@@ -739,15 +811,11 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
         lds_sync();
         if (s_flag[0] == 0) {  // uniform: every thread reads the same flag
           const int n = min(s_cnt[ep], C::QCAP);
-          for (int i = esub; i < n; i += C::TPP) {
+          for (int i = consumer ? esub : n; i < n; i += C::TPP) {
             const uint2 e = reinterpret_cast<const uint2*>(sq)[qslot(ep, i)];
             const uint64_t key = make_key(__uint_as_float(e.x), e.y);
             if (key > list[KP - 1]) list_insert(list, key);
           }
-#pragma unroll
-          for (int x = 0; x < C::TV; ++x)
-#pragma unroll
-            for (int y = 0; y < C::TR; ++y) acc[x][y] = floatx4{0.f, 0.f, 0.f, 0.f};
           publish_floors();
           continue;  // the next slice's barrier ends every read of the queues
         }
@@ -770,20 +838,21 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
           for (int y = 0; y < C::TR; ++y) {
             const int p = wr * C::WR + y * 16 + l15;
             *reinterpret_cast<floatx4*>(sE + p * C::EPI_V + epi_slot(p, wv * 4 + (lane >> 4)) * 4) = acc[xs][y];
-            acc[xs][y] = floatx4{0.f, 0.f, 0.f, 0.f};
           }
         }
       }
       lds_sync();
 #pragma unroll (kOneConsume ? 1 : kColUnroll)
-      for (int col = esub * 4; col < C::EPI_V; col += C::TPP * 4)
+      for (int col = consumer ? esub * 4 : C::EPI_V; col < C::EPI_V; col += C::TPP * 4)
         consume(sE, x, col, v0, vend);
       // Share the floors of a row's TPP lists: each thread's floor bounds the
       // row's KP-th largest key from below, so the largest of them filters
       // every list of the row.  It pays on the large-row tile (two lists per
       // row, long streams); with eight lists per row and short streams the
       // exchange costs more than the insertions it saves.
-      if constexpr (kRowThreshold && C::TPP == 2) s_thr[ep * C::TPP + esub] = thr;
+      if constexpr (kRowThreshold && C::TPP == 2) {
+        if (consumer) s_thr[ep * C::TPP + esub] = thr;
+      }
       lds_sync();
       if constexpr (kRowThreshold && C::TPP == 2) {
 #pragma unroll
@@ -1012,8 +1081,18 @@ using SmallRows = TileCfg<64, 32, 4, 1, 256, 3>;
 // 64-key lists take 128 registers: at two waves per SIMD they would spill,
 // so that case keeps the fold in the compute waves.
 using SmallRowsUnsplit = TileCfg<64, 32, 4, 1, 256, 3, false>;
-using MidRows = TileCfg<256, 64, 4, 1, 64, 3>;      // <= 64 rows
-using LargeRows = TileCfg<256, 256, 4, 2, 64, 2>;   // many rows: MFMA bound
+// 33-64 and 65-128 rows: lm_head streams too, three slices deep; eight waves
+// fold filtered survivors as the larger tiles do.  On one box, against the
+// tiles these shapes ran on before (126464 x 4096): 64 rows 206 -> 183 us (4
+// waves, lists folded from staged logits), 96 rows 239 -> 192 and 128 rows
+// 247 -> 193 us (256-row tile).
+using Rows64 = TileCfg<256, 64, 4, 2, 64, 3>;
+using Rows128 = TileCfg<256, 128, 4, 2, 64, 3>;
+// many rows: MFMA bound.  192-row tiles where they leave less padding.
+using Rows192 = TileCfg<256, 192, 4, 2, 64, 2>;
+using Rows256 = TileCfg<256, 256, 4, 2, 64, 2>;
+// sampling pass, and lists longer than kFiltKeys, at 33-64 rows
+using MidRows = TileCfg<256, 64, 4, 1, 64, 3>;
 
 constexpr int kTargetWorkgroups = 256;  // one persistent workgroup per compute unit
 // The plain pass at 32 rows or fewer streams lm_head as fast from 224
@@ -1025,7 +1104,7 @@ constexpr int kTargetWorkgroups = 256;  // one persistent workgroup per compute 
 constexpr int kSmallRowsWorkgroups = 224;
 
 struct Plan {
-  int cfg;  // 0 small, 1 mid, 2 large
+  int cfg;  // row tile: 0 -> 32 rows, 1 -> 64, 2 -> 128, 3 -> 192, 4 -> 256
   int n_rtiles, n_vtiles, tiles_per_group, n_groups, n_parts, KP;
   int even;  // equal vocabulary shares instead of runs of whole tiles
 };
@@ -1036,35 +1115,54 @@ Plan make_plan_for(int cfg, int rows, int V, int K, int target = kTargetWorkgrou
   p.cfg = cfg;
   p.n_rtiles = (rows + C::BR - 1) / C::BR;
   p.n_vtiles = (V + C::BV - 1) / C::BV;
-  int want = target / p.n_rtiles;
-  want = want < 1 ? 1 : (want > p.n_vtiles ? p.n_vtiles : want);
-  p.tiles_per_group = (p.n_vtiles + want - 1) / want;
-  p.n_groups = (p.n_vtiles + p.tiles_per_group - 1) / p.tiles_per_group;
-  // Weight-streaming shapes: when runs of whole tiles leave compute units
-  // idle, cut the vocabulary into one equal share per compute unit instead
-  // (the partly masked last tile costs MFMA time, which these shapes have
-  // to spare, but no memory traffic).
-  const int want_all = target / p.n_rtiles < 1 ? 1 : target / p.n_rtiles;
-  p.even = 0;
-  if (kEvenShares && cfg != 2 && p.n_groups < want_all && V / want_all >= C::BV / 2) {
-    p.even = 1;
-    p.n_groups = want_all;
-    p.tiles_per_group = (V / want_all + 16 + C::BV - 1) / C::BV;
-  }
   p.KP = K <= 4 ? 4 : K <= 8 ? 8 : K <= 16 ? 16 : K <= 32 ? 32 : 64;
   const bool wg_merge = p.KP == 4    ? kWgMerge<C, 4>
                         : p.KP == 8  ? kWgMerge<C, 8>
                         : p.KP == 16 ? kWgMerge<C, 16>
                         : p.KP == 32 ? kWgMerge<C, 32>
                                      : kWgMerge<C, 64>;
-  p.n_parts = p.n_groups * (wg_merge ? 1 : C::TPP);
+  const int lists = wg_merge ? 1 : C::TPP;  // per row and group
+  int want = target / p.n_rtiles;
+  want = want < 1 ? 1 : (want > p.n_vtiles ? p.n_vtiles : want);
+  p.tiles_per_group = (p.n_vtiles + want - 1) / want;
+  p.n_groups = (p.n_vtiles + p.tiles_per_group - 1) / p.tiles_per_group;
+  // When runs of whole tiles leave compute units idle, cut the vocabulary
+  // into one equal share per compute unit instead (the partly masked last
+  // tile costs MFMA time but no memory traffic).  Lists longer than kFiltKeys
+  // keep whole tiles on the 256-row tile: more shares would mean more key
+  // lists, past the no-alloc scratch for shapes that fit it.
+  const int want_all = target / p.n_rtiles < 1 ? 1 : target / p.n_rtiles;
+  p.even = 0;
+  if ((p.KP <= kFiltKeys || C::WAVES_R == 1) && p.n_groups < want_all && V / want_all >= C::BV / 2) {
+    p.even = 1;
+    p.n_groups = want_all;
+    p.tiles_per_group = (V / want_all + 16 + C::BV - 1) / C::BV;
+  }
+  p.n_parts = p.n_groups * lists;
   return p;
+}
+
+// Time of a pass in arbitrary units: the tiles of the longest share times the
+// tile's time per reduction slice.  4096 rows x 126464 tokens took 1.00, 1.47
+// and 1.69 us a slice on the 128-, 192- and 256-row tiles.
+int plan_cost(const Plan& p, int V, int slice) {
+  const int share = (V + p.n_groups - 1) / p.n_groups;
+  return (p.even ? (share + 255) / 256 : p.tiles_per_group) * slice;
 }
 
 Plan make_plan(int rows, int V, int K, bool sample = false) {
   if (rows <= 32) return make_plan_for<SmallRows>(0, rows, V, K, sample ? kTargetWorkgroups : kSmallRowsWorkgroups);
-  if (rows <= 64) return make_plan_for<MidRows>(1, rows, V, K);
-  return make_plan_for<LargeRows>(2, rows, V, K);
+  // the sampling pass and lists longer than kFiltKeys fold staged logits
+  if (sample || K > kFiltKeys) return rows <= 64 ? make_plan_for<MidRows>(1, rows, V, K) : make_plan_for<Rows256>(4, rows, V, K);
+  if (rows <= 64) return make_plan_for<Rows64>(1, rows, V, K);
+  // Above 64 rows, the tile with the least padding by plan_cost.  Measured at
+  // 126464 x 4096, 128- / 192- / 256-row tile in us: 192 rows 298 / 258 / 270,
+  // 256 rows 315 / 394 / 286, 320 rows 425 / 416 / 437, 512 rows 564 / 599 /
+  // 493, 768 rows 811 / 783 / 707, 4096 rows 3974 / 4221 / 3352.
+  const Plan p2 = make_plan_for<Rows128>(2, rows, V, K), p3 = make_plan_for<Rows192>(3, rows, V, K),
+             p4 = make_plan_for<Rows256>(4, rows, V, K);
+  const int c2 = plan_cost(p2, V, 20), c3 = plan_cost(p3, V, 29), c4 = plan_cost(p4, V, 34);
+  return c4 <= c2 && c4 <= c3 ? p4 : (c3 <= c2 ? p3 : p2);
 }
 
 template <class C, int KP, bool SAMPLE = false>
@@ -1272,8 +1370,16 @@ void launch_kp_pass(const Plan& p, const uint16_t* H, const uint16_t* W, int row
       if constexpr (KP >= 64) launch_tile<SmallRowsUnsplit, KP>(p, H, W, rows, d, V, partial, s);
       else launch_tile<SmallRows, KP>(p, H, W, rows, d, V, partial, s);
       break;
-    case 1: launch_tile<MidRows, KP>(p, H, W, rows, d, V, partial, s); break;
-    default: launch_tile<LargeRows, KP>(p, H, W, rows, d, V, partial, s); break;
+    default:
+      if constexpr (KP <= kFiltKeys) {
+        if (p.cfg == 1) launch_tile<Rows64, KP>(p, H, W, rows, d, V, partial, s);
+        else if (p.cfg == 2) launch_tile<Rows128, KP>(p, H, W, rows, d, V, partial, s);
+        else if (p.cfg == 3) launch_tile<Rows192, KP>(p, H, W, rows, d, V, partial, s);
+        else launch_tile<Rows256, KP>(p, H, W, rows, d, V, partial, s);
+      } else {
+        if (p.cfg == 1) launch_tile<MidRows, KP>(p, H, W, rows, d, V, partial, s);
+        else launch_tile<Rows256, KP>(p, H, W, rows, d, V, partial, s);
+      }
   }
 }
 
@@ -1297,7 +1403,7 @@ void launch_spec_kp(const Plan& p, const uint16_t* Hv, const uint16_t* W, int B,
   switch (p.cfg) {
     case 0: launch_tile<SmallRows, KP, true>(p, Hv, W, rows, d, V, partial, s, sa); break;
     case 1: launch_tile<MidRows, KP, true>(p, Hv, W, rows, d, V, partial, s, sa); break;
-    default: launch_tile<LargeRows, KP, true>(p, Hv, W, rows, d, V, partial, s, sa); break;
+    default: launch_tile<Rows256, KP, true>(p, Hv, W, rows, d, V, partial, s, sa); break;
   }
   hipLaunchKernelGGL((spec_row_kernel<KP>), dim3(rows), dim3(256), 0, s, partial, sa.lse_part, p.n_parts,
                      Hv, W, d, V, K, proposal, cand_id, cand_prob, u_accept, sa.inv_T, sa.key0, sa.key1,
