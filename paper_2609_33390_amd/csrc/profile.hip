@@ -11,9 +11,13 @@
 // w_i = M w_raw_i / (sum_j w_raw_j + eps).
 //
 // Two launches: workgroups histogram disjoint slices of the lengths into
-// private partial histograms (no atomics on global memory, so the counts do
-// not depend on scheduling), then one workgroup adds the partials and
-// evaluates the closed forms in fp64.
+// partial histograms (no atomics on global memory, so the counts do not depend
+// on scheduling), then one workgroup adds the partials and evaluates the
+// closed forms in fp64, one position per thread, with scans for the products
+// and sums.  Both are bound by latency, so what counts is the number of
+// dependent steps: at 2^20 lengths, M = 32, the pair took 15.6 + 11.8 us with
+// a barrier pair per bin in the first and serial loops over the positions in
+// the second, and takes 6.2 + 6.6 us.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -30,133 +34,139 @@ int hist_groups(int n_blocks) {
   return g < 1 ? 1 : (g > kMaxHistGroups ? kMaxHistGroups : g);
 }
 
+// Columns of counters per bin, and the LDS they take: one per thread while 64
+// KiB hold them, fewer for larger M (threads of one column then add in turn).
+constexpr int hist_cols(int M) { return M < 64 ? 256 : M < 256 ? 64 : M < 512 ? 16 : 8; }
+
+// Partial histogram of this workgroup's slice: part[j * groups + workgroup].
+template <int COLS>
 __global__ __launch_bounds__(kHistThreads) void accept_hist_kernel(const int32_t* __restrict__ len,
                                                                    int n_blocks, int M,
                                                                    uint32_t* __restrict__ part) {
-  // M < 64: every thread owns a private column of counters (no atomics, no
-  // conflicting updates); otherwise one shared histogram with LDS atomics
-  extern __shared__ uint32_t h[];
-  const bool priv = M < kWave;
-  const int cols = priv ? kHistThreads : 1;
-  for (int j = threadIdx.x; j < (M + 1) * cols; j += kHistThreads) h[j] = 0;
-  __syncthreads();
+  extern __shared__ __align__(16) uint32_t h[];  // [M + 1][COLS]
+  const int tid = threadIdx.x;
   const int per = (n_blocks + gridDim.x - 1) / gridDim.x;
   const int b0 = blockIdx.x * per;
   const int b1 = min(b0 + per, n_blocks);
-  constexpr int BATCH = 8;
+  // a slice of 4096 lengths is one batch: all its loads in flight at once
+  constexpr int BATCH = 16;
+  int Ls[BATCH];
+  auto load = [&](int bb) {
+#pragma unroll
+    for (int q = 0; q < BATCH; ++q) {
+      const int b = bb + q * kHistThreads + tid;
+      Ls[q] = b < b1 ? len[b] : 0;
+    }
+  };
+  load(b0);
+  for (int j = tid; j < (M + 1) * (COLS / 4); j += kHistThreads)
+    reinterpret_cast<uint4*>(h)[j] = make_uint4(0, 0, 0, 0);
+  __syncthreads();
   for (int bb = b0; bb < b1; bb += kHistThreads * BATCH) {
-    int Ls[BATCH];
 #pragma unroll
     for (int q = 0; q < BATCH; ++q) {
-      const int b = bb + q * kHistThreads + threadIdx.x;
-      Ls[q] = b < b1 ? len[b] : -1;
-    }
-#pragma unroll
-    for (int q = 0; q < BATCH; ++q) {
-      const int b = bb + q * kHistThreads + threadIdx.x;
-      if (b >= b1) continue;
       const int L = Ls[q] < 0 ? 0 : (Ls[q] > M ? M : Ls[q]);
-      if (priv) h[L * kHistThreads + threadIdx.x] += 1u;
-      else atomicAdd(&h[L], 1u);
+      // additions without a result do not wait for each other
+      if (bb + q * kHistThreads + tid < b1) atomicAdd(&h[L * COLS + tid % COLS], 1u);
     }
+    if (bb + kHistThreads * BATCH < b1) load(bb + kHistThreads * BATCH);
   }
   __syncthreads();
-  if (priv) {
-    // bin j: sum of the 256 private counters (each thread adds its row of 4)
-    for (int j = 0; j <= M; ++j) {
-      uint32_t v = h[j * kHistThreads + threadIdx.x];
-      v += __shfl_xor(v, 1, kWave);
-      v += __shfl_xor(v, 2, kWave);
-      v += __shfl_xor(v, 4, kWave);
-      v += __shfl_xor(v, 8, kWave);
-      v += __shfl_xor(v, 16, kWave);
-      v += __shfl_xor(v, 32, kWave);
-      __syncthreads();
-      if ((threadIdx.x & 63) == 0) h[j * kHistThreads + threadIdx.x] = v;  // wave totals in place
-      __syncthreads();
-      if (threadIdx.x == 0)
-        part[static_cast<size_t>(blockIdx.x) * (M + 1) + j] =
-            h[j * kHistThreads] + h[j * kHistThreads + 64] + h[j * kHistThreads + 128] + h[j * kHistThreads + 192];
+  // four counters a lane, COLS / 4 lanes a bin
+  constexpr int LPB = COLS / 4, BPI = kHistThreads / LPB;
+  for (int j0 = 0; j0 <= M; j0 += BPI) {
+    const int j = j0 + tid / LPB;
+    uint32_t v = 0;
+    if (j <= M) {
+      const uint4 c = reinterpret_cast<const uint4*>(h)[j * LPB + tid % LPB];
+      v = (c.x + c.y) + (c.z + c.w);
     }
-  } else {
-    for (int j = threadIdx.x; j <= M; j += kHistThreads)
-      part[static_cast<size_t>(blockIdx.x) * (M + 1) + j] = h[j];
+#pragma unroll
+    for (int off = 1; off < LPB; off <<= 1) v += __shfl_xor(v, off, kWave);
+    if (j <= M && tid % LPB == 0) part[static_cast<size_t>(j) * gridDim.x + blockIdx.x] = v;
   }
 }
 
-__global__ __launch_bounds__(kHistThreads) void accept_profile_kernel(const uint32_t* __restrict__ part,
-                                                                      int groups, int M, double eps,
+constexpr int kProfThreads = 1024, kProfWaves = kProfThreads / kWave;
+static_assert(kProfThreads >= 1024, "one position per thread");
+
+// Inclusive scan over the threads of the workgroup, towards higher threads
+// (UP) or lower ones: the wave's own scan, then the totals of the waves
+// before it, in order.  `ident` is op's neutral element; s holds kProfWaves
+// values, and the caller puts a barrier between two uses of it.
+template <bool UP, class T, class Op>
+__device__ __forceinline__ T block_scan(T v, T ident, Op op, T* s) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const T o = UP ? __shfl_up(v, off, kWave) : __shfl_down(v, off, kWave);
+    if (UP ? lane >= off : lane + off < kWave) v = op(v, o);
+  }
+  if (lane == (UP ? kWave - 1 : 0)) s[wave] = v;
+  __syncthreads();
+  T before = ident;
+  for (int w = 0; w < kProfWaves; ++w)
+    if (UP ? w < wave : w > wave) before = op(before, s[w]);
+  return op(v, before);
+}
+
+__global__ __launch_bounds__(kProfThreads) void accept_profile_kernel(const uint32_t* __restrict__ part,
+                                                                      int groups, int n_blocks, int M, double eps,
                                                                       double* __restrict__ a_out,
                                                                       double* __restrict__ raw_out,
                                                                       double* __restrict__ w_out,
                                                                       double* __restrict__ tpf_fpt) {
-  extern __shared__ double sm[];
-  double* cnt = sm;              // [M + 1] block counts per accepted length
-  __shared__ uint32_t c32[1025];
-  double* a = cnt + (M + 1);     // [M]
-  double* A = a + M;             // [M + 1] survival
-  double* S = A + (M + 1);       // [M + 1] S_i = sum_{k=i}^{M-1} A_k
-  double* R = S + (M + 1);       // [M] raw sensitivities
-  __shared__ double s_num, s_den, s_sum;
-  // add the partial histograms: every (group, length) entry is one load, a
-  // batch of loads in flight per thread, integer LDS atomics (order-free)
-  for (int j = threadIdx.x; j <= M; j += kHistThreads) c32[j] = 0;
-  __syncthreads();
-  const int n_ent = groups * (M + 1);
-  constexpr int BATCH = 8;
-  for (int e0 = 0; e0 < n_ent; e0 += kHistThreads * BATCH) {
-    uint32_t v[BATCH];
+  __shared__ uint32_t cnt[1025];  // blocks per accepted length
+  __shared__ uint32_t s_u[kProfWaves];
+  __shared__ double s_a[kProfWaves], s_b[kProfWaves], s_c[kProfWaves], s_end[2];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  // a wavefront adds the partials of two bins at a time, their loads together
+  static_assert(kMaxHistGroups <= 4 * kWave, "four partials a lane");
+  for (int j0 = wave; j0 <= M; j0 += 2 * kProfWaves) {
+    uint32_t v[2][4];
 #pragma unroll
-    for (int q = 0; q < BATCH; ++q) {
-      const int e = e0 + q * kHistThreads + threadIdx.x;
-      v[q] = e < n_ent ? part[e] : 0u;
-    }
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int q = 0; q < BATCH; ++q) {
-      const int e = e0 + q * kHistThreads + threadIdx.x;
-      if (e < n_ent && v[q]) atomicAdd(&c32[e % (M + 1)], v[q]);
+      for (int q = 0; q < 4; ++q) {
+        const int j = j0 + i * kProfWaves, g = lane + q * kWave;
+        v[i][q] = j <= M && g < groups ? part[static_cast<size_t>(j) * groups + g] : 0u;
+      }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      uint32_t c = (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) c += __shfl_xor(c, off, kWave);
+      if (lane == 0 && j0 + i * kProfWaves <= M) cnt[j0 + i * kProfWaves] = c;
     }
   }
   __syncthreads();
-  for (int j = threadIdx.x; j <= M; j += kHistThreads) cnt[j] = static_cast<double>(c32[j]);
+  // position i = t + 1: reached_i = #{L >= i - 1}, rejected_i = #{L = i - 1}
+  const bool on = t < M;
+  const uint32_t rej = on ? cnt[t] : 0u;
+  const auto add = [](auto x, auto y) { return x + y; };
+  const uint32_t upto = block_scan<true>(rej, 0u, add, s_u);  // #{L <= i - 1}
+  const double reach = static_cast<double>(static_cast<uint32_t>(n_blocks) - (upto - rej));
+  const double a = on && reach > 0.0 ? 1.0 - static_cast<double>(rej) / reach : 1.0;
+  const double A = block_scan<true>(a, 1.0, [](double x, double y) { return x * y; }, s_a);  // A_i
+  // S_i = sum_{k=i}^{M-1} A_k
+  const double S = block_scan<false>(t < M - 1 ? A : 0.0, 0.0, add, s_b);
+  if (t == 0) s_end[0] = S;
+  if (t == M - 1) s_end[1] = A;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    // reached_i = #{L >= i-1}, rejected_i = #{L = i-1}
-    double reach = 0.0;
-    for (int j = 0; j <= M; ++j) reach += cnt[j];
-    for (int i = 1; i <= M; ++i) {
-      const double rej = cnt[i - 1];
-      a[i - 1] = reach > 0.0 ? 1.0 - rej / reach : 1.0;
-      reach -= rej;
-    }
-    A[0] = 1.0;
-    for (int k = 1; k <= M; ++k) A[k] = A[k - 1] * a[k - 1];
-    double num = 2.0;
-    for (int k = 1; k <= M - 1; ++k) num += A[k];
-    S[M] = 0.0;
-    for (int i = M - 1; i >= 1; --i) S[i] = S[i + 1] + A[i];
-    s_num = num;
-    s_den = 2.0 - A[M];
-  }
-  __syncthreads();
-  const double num = s_num, den = s_den;
-  for (int i = 1 + threadIdx.x; i <= M; i += kHistThreads) {
-    const double Si = i <= M - 1 ? S[i] : 0.0;
-    const double r = (1.0 - a[i - 1]) * (A[M] * num + den * Si) / (num * num);
-    raw_out[i - 1] = r;
-    a_out[i - 1] = a[i - 1];
-    R[i - 1] = r;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double sum = 0.0;
-    for (int i = 0; i < M; ++i) sum += R[i];
-    s_sum = sum;
+  const double num = 2.0 + s_end[0], den = 2.0 - s_end[1];
+  const double R = on ? (1.0 - a) * (s_end[1] * num + den * S) / (num * num) : 0.0;
+  const double sum_from = block_scan<false>(R, 0.0, add, s_c);
+  if (t == 0) {
+    s_end[0] = sum_from;  // read above, before block_scan's barrier
     tpf_fpt[0] = num / den;
     tpf_fpt[1] = den / num;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < M; i += kHistThreads) w_out[i] = M * R[i] / (s_sum + eps);
+  if (on) {
+    a_out[t] = a;
+    raw_out[t] = R;
+    w_out[t] = M * R / (s_end[0] + eps);
+  }
 }
 
 }  // namespace
@@ -169,11 +179,16 @@ void launch_accept_profile(const int32_t* accept_len, int n_blocks, int M, doubl
                            double* w_raw, double* w, double* tpf_fpt, void* ws, hipStream_t s) {
   const int groups = hist_groups(n_blocks);
   uint32_t* part = static_cast<uint32_t*>(ws);
-  const size_t hist_lds = (M + 1) * sizeof(uint32_t) * (M < kWave ? kHistThreads : 1);
-  hipLaunchKernelGGL(accept_hist_kernel, dim3(groups), dim3(kHistThreads), hist_lds, s,
-                     accept_len, n_blocks, M, part);
-  hipLaunchKernelGGL(accept_profile_kernel, dim3(1), dim3(kHistThreads), (5 * M + 3) * sizeof(double), s,
-                     part, groups, M, eps, a, w_raw, w, tpf_fpt);
+  const size_t hist_lds = static_cast<size_t>(M + 1) * hist_cols(M) * sizeof(uint32_t);
+  const dim3 g(groups), b(kHistThreads);
+  switch (hist_cols(M)) {
+    case 256: hipLaunchKernelGGL(accept_hist_kernel<256>, g, b, hist_lds, s, accept_len, n_blocks, M, part); break;
+    case 64: hipLaunchKernelGGL(accept_hist_kernel<64>, g, b, hist_lds, s, accept_len, n_blocks, M, part); break;
+    case 16: hipLaunchKernelGGL(accept_hist_kernel<16>, g, b, hist_lds, s, accept_len, n_blocks, M, part); break;
+    default: hipLaunchKernelGGL(accept_hist_kernel<8>, g, b, hist_lds, s, accept_len, n_blocks, M, part); break;
+  }
+  hipLaunchKernelGGL(accept_profile_kernel, dim3(1), dim3(kProfThreads), 0, s, part, groups, n_blocks, M, eps, a,
+                     w_raw, w, tpf_fpt);
 }
 
 }  // namespace brisk

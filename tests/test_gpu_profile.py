@@ -81,3 +81,11 @@ def test_profile_deterministic_repeat():
     torch.cuda.synchronize()
     for k in g1:
         assert torch.equal(g1[k], g2[k])
+
+
+@pytest.mark.parametrize("n,M", [(4095, 63), (4096, 64), (4097, 65), (70_000, 255), (70_000, 256), (9000, 511),
+                                 (9000, 512), (300, 1023), (1_100_000, 2)])
+def test_profile_at_the_edges_of_the_histogram_forms(n, M):
+    """Either side of each counter-column count, of one batch of 4096 lengths
+    and of 256 partial histograms."""
+    _compare(_lengths(n, min(M, 64), np.full(min(M, 64), 0.93), n + M) * max(1, M // 64), M, 1e-12)
