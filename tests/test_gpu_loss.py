@@ -55,3 +55,22 @@ def test_loss_ragged_and_scaled_corrector(B, L, K, d, V):
     g, o = _run(wl, psi_std=0.2)
     _check(g, o)
     assert 0 < o["count"] <= B * L
+
+
+@pytest.mark.parametrize("B,L,K,d,V", [(3, 5, 4, 4096, 500), (3, 5, 5, 4104, 500), (2, 6, 9, 520, 300),
+                                       (1100, 1, 8, 64, 300), (41, 100, 1, 8, 300)])
+def test_loss_at_the_edges_of_its_batches(B, L, K, d, V):
+    """Candidates either side of a pair and of a round of pairs, d either side
+    of one round of loads and of a chunk, rows either side of the mean's batch."""
+    g = torch.Generator().manual_seed(B + d)
+    rows = B * L
+    Hv, W = (torch.randn(n, d, generator=g).to(torch.bfloat16) for n in (rows, V))
+    W = (W.float() * d ** -0.5).to(torch.bfloat16)
+    ci = torch.rand(rows, V, generator=g).argsort(1)[:, :K].to(torch.int32).contiguous()
+    cl, ref = (torch.randn(rows, K, generator=g) for _ in range(2))
+    acc = torch.randint(0, L + 1, (B,), generator=g).to(torch.int32)
+    out = brisk.corrector_loss(*(t.cuda() for t in (Hv, W, ci, cl, ref, acc)), B, L)
+    torch.cuda.synchronize()
+    o = oracle.corrector_loss(oracle.bf16_to_f64(synth.bf16_bits(Hv)), synth.bf16_bits(W), ci.numpy(),
+                              cl.double().numpy(), ref.double().numpy(), acc.numpy(), L)
+    _check({k: v.cpu().numpy() for k, v in out.items()}, o)
