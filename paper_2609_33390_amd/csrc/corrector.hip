@@ -657,6 +657,331 @@ __global__ __launch_bounds__(256) void lift_kernel(LiftJobs jobs) {
 }
 
 // ---------------------------------------------------------------------------
+// Per-token tables (brisk_corrector_prepare).
+//
+// table_proj: out[n, j] = sum_k table[n, k] * wt[j, k] for every token n, the
+// same sums in the same order as gather_proj.  It streams both embedding
+// matrices once (2.07 GB at 126464 x 4096), so tiles are 256 tokens x 128
+// outputs, copied straight into LDS three 64-wide slices deep, and persistent
+// workgroups run through their share as one stream: the weights are re-read
+// from L2 once per 256 tokens, where gather_proj's 64-token tiles re-read
+// them four times as often.  At 128 outputs each: 595 us as gather_proj, 535
+// as one workgroup per tile, 482 persistent, 415-439 (5.0 TB/s) with the
+// tokens read non-temporally.
+// ---------------------------------------------------------------------------
+struct TableProjJob {
+  const uint16_t* table;  // [n, d]
+  const uint16_t* wt;     // [J, d]
+  float* out;             // [n, J]
+  int n, J;
+};
+struct TableProjJobs {
+  TableProjJob job[2];
+  int d;
+};
+constexpr int TP_BN = 256, TP_BJ = 128, TP_BK = 64, TP_STAGES = 3, TP_NW = 8;
+constexpr int TP_CPR = TP_BK / 8;                             // 16-byte chunks per staged row
+constexpr int TP_STAGE = (TP_BN + TP_BJ) * TP_BK * 2;         // bytes
+constexpr int TP_NDMA = (TP_BN + TP_BJ) / 8 / TP_NW;          // copies per wave and slice, 8 rows each
+static_assert(TP_STAGES * TP_STAGE <= 160 * 1024, "LDS");
+// Cache policy of the token copies: non-temporal, so that the stream, which is
+// read once, does not push the weights out of L2 (482 against 415 us).
+constexpr int kStreamAux = 2;
+
+// One workgroup per compute unit (its LDS): two waves per SIMD.
+__global__ __launch_bounds__(64 * TP_NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void table_proj_kernel(
+    TableProjJobs jobs) {
+  __shared__ __align__(16) unsigned char smem[TP_STAGES * TP_STAGE];
+  // workgroups are dealt round-robin to the 8 XCDs: each XCD takes a
+  // contiguous range of shares
+  const int per_xcd = static_cast<int>(gridDim.x) / 8;
+  const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8, shares = static_cast<int>(gridDim.x) / 2;
+  const TableProjJob& jb = jobs.job[logical / shares];
+  const int d = jobs.d;
+  // this workgroup's tokens [nb, ne), cut at multiples of 16, as one stream
+  // of slices over its tiles
+  const int sh = logical % shares;
+  const int nb = static_cast<int>(static_cast<long long>(sh) * jb.n / shares) & ~15;
+  const int ne = sh + 1 == shares ? jb.n : static_cast<int>(static_cast<long long>(sh + 1) * jb.n / shares) & ~15;
+  const int j0 = blockIdx.y * TP_BJ;
+  if (nb >= ne || j0 >= jb.J) return;
+  const int n_tiles = (ne - nb + TP_BN - 1) / TP_BN;
+  const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = wave & 3, wj = wave >> 2;  // 64 tokens x 64 outputs a wave
+  const unsigned row_bytes = static_cast<unsigned>(d) * 2u;
+  const int nj = min(TP_BJ, jb.J - j0);
+  // Rows past the share's read as zeros without memory traffic.  The resource
+  // of the tokens is moved to the tile, so offsets fit 32 bits (256 rows of
+  // at most 131072 bytes).
+  auto token_rsrc = [&](int tl) {
+    const int n0 = nb + tl * TP_BN;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(jb.table + static_cast<size_t>(n0) * d),
+                                             static_cast<short>(0),
+                                             static_cast<int>(static_cast<unsigned>(min(TP_BN, ne - n0)) * row_bytes), 0x00020000);
+  };
+  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(jb.wt + static_cast<size_t>(j0) * d), static_cast<short>(0),
+      static_cast<int>(static_cast<unsigned>(nj) * row_bytes), 0x00020000);
+  // staged rows are 128 bytes; chunk c of row r sits in slot c ^ (r & 7), so
+  // the operand reads (16 rows, one chunk) are free of bank conflicts
+  const unsigned lane_voff = static_cast<unsigned>(lane >> 3) * row_bytes + static_cast<unsigned>((lane & 7) ^ (lane >> 3)) * 16u;
+  const int nk = (d + TP_BK - 1) / TP_BK, tail = (d % TP_BK) / 8;
+  // copies run TP_STAGES - 1 slices ahead of the products
+  int is_g = 0, is_tl = 0, is_kt = 0;
+  __amdgpu_buffer_rsrc_t rt = token_rsrc(0);
+  auto issue = [&] {
+    if (is_tl >= n_tiles) return;
+    const unsigned k0b = static_cast<unsigned>(is_kt * TP_BK) * 2u;
+    unsigned char* base = smem + (is_g % TP_STAGES) * TP_STAGE;
+#pragma unroll
+    for (int i = 0; i < TP_NDMA; ++i) {
+      const int q = i * TP_NW + wave;  // 8 staged rows a copy: tokens, then outputs
+      if (q * 8 < TP_BN)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rt, (__attribute__((address_space(3))) void*)(base + q * 1024), 16,
+                                                 lane_voff + static_cast<unsigned>(q * 8) * row_bytes + k0b, 0, 0, kStreamAux);
+      else
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rp, (__attribute__((address_space(3))) void*)(base + q * 1024), 16,
+                                                 lane_voff + static_cast<unsigned>(q * 8 - TP_BN) * row_bytes + k0b, 0, 0, 0);
+    }
+    ++is_g;
+    if (++is_kt == nk) {
+      is_kt = 0;
+      if (++is_tl < n_tiles) rt = token_rsrc(is_tl);
+    }
+  };
+  int lane_off[2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) lane_off[kk] = (l15 * TP_CPR + ((kk * 4 + (lane >> 4)) ^ (l15 & 7))) * 16;
+  const bool vec = (jb.J & 3) == 0 && (reinterpret_cast<uintptr_t>(jb.out) & 15u) == 0;
+#pragma unroll
+  for (int g = 0; g < TP_STAGES - 1; ++g) issue();
+  for (int tl = 0; tl < n_tiles; ++tl) {
+    floatx4 acc[4][4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) acc[x][y] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int kt = 0; kt < nk; ++kt) {
+      const int g = tl * nk + kt;
+      // slice g has landed, and every wave is done reading slice g - 1.  The
+      // last slices have fewer younger copies, and the first of a tile has the
+      // stores of the tile before among them: they wait for all.
+      constexpr int kYounger = (TP_STAGES - 2) * TP_NDMA;
+      if (g + TP_STAGES - 2 < n_tiles * nk && (kt >= TP_STAGES - 1 || tl == 0))
+        __builtin_amdgcn_s_waitcnt((kYounger & 15) | (((kYounger >> 4) & 3) << 14) | (7 << 4) | (0 << 8));
+      else
+        __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0 << 8));
+      asm volatile("s_barrier" ::: "memory");
+      issue();
+      unsigned char* sb = smem + (g % TP_STAGES) * TP_STAGE;
+      if (tail && kt == nk - 1) {
+        // chunks past d hold the next row's data: zero them in both tiles
+        const int nz = TP_CPR - tail;
+        for (int idx = tid; idx < (TP_BN + TP_BJ) * nz; idx += 64 * TP_NW) {
+          const int R = idx / nz, c = tail + idx % nz;
+          *reinterpret_cast<uint4*>(sb + (R * TP_CPR + (c ^ (R & 7))) * 16) = make_uint4(0, 0, 0, 0);
+        }
+        __syncthreads();
+      }
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        bf16x8 a[4], b[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+          a[x] = *reinterpret_cast<const bf16x8*>(sb + (TP_BN + wj * 64 + x * 16) * TP_CPR * 16 + lane_off[kk]);
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+          b[y] = *reinterpret_cast<const bf16x8*>(sb + (wn * 64 + y * 16) * TP_CPR * 16 + lane_off[kk]);
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int y = 0; y < 4; ++y)
+            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], b[y], acc[x][y], 0, 0, 0);
+      }
+    }
+    // lane: outputs 16 x + 4 (lane / 16) + q of token 16 y + lane % 16
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const int n = nb + tl * TP_BN + wn * 64 + y * 16 + l15;
+      if (n >= ne) continue;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int j = j0 + wj * 64 + x * 16 + (lane >> 4) * 4;
+        float* o = jb.out + static_cast<size_t>(n) * jb.J + j;
+        if (vec) {
+          if (j < jb.J) *reinterpret_cast<float4*>(o) = make_float4(acc[x][y][0], acc[x][y][1], acc[x][y][2], acc[x][y][3]);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (j + q < jb.J) o[q] = acc[x][y][q];
+        }
+      }
+    }
+  }
+}
+
+// table_lift: out[n, j] = sum_c M(j, c) in[n, c] for every token n and one or
+// two matrices of the same input, with lift's three-term split of the fp32
+// input and its order of products.  A wave keeps the split operands of its 16
+// tokens in registers (NK 32-wide steps) and walks all output columns, so the
+// input is read and split once; lift's 64 x 64 tiles do both four times per
+// matrix.  At 126464 tokens, 128 columns in and 256 out: 234 us as lift, 171-187
+// here, 162 with non-temporal stores (517 MB of inputs and tables, 3.2 TB/s).
+struct TableLiftMat {
+  const uint16_t* m;  // M(j, c) = m[j * m_rs + c * m_cs]
+  int m_rs, m_cs;
+  int vec;            // 1: 16-byte vectors along c; 2: along j; 0: neither
+  float* out;         // [n][vs]
+};
+struct TableLiftJob {
+  const float* in;  // [n, C]
+  int C, n_mats;
+  TableLiftMat mat[2];
+};
+struct TableLiftJobs {
+  TableLiftJob job[2];
+  int n, ds, vs;
+};
+constexpr int TL_NW = 8, TL_BN = 16 * TL_NW, TL_BJ = 64;
+
+template <int NK>
+__global__ __launch_bounds__(64 * TL_NW) void table_lift_kernel(TableLiftJobs jobs) {
+  constexpr int KC = NK * 32, ROW = KC + 8;  // staged matrix row: KC columns, padded against bank conflicts
+  __shared__ __align__(16) uint16_t s_m[2][TL_BJ * ROW];
+  const TableLiftJob& jb = jobs.job[blockIdx.y];
+  const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, wave = tid >> 6;
+  const int ds = jobs.ds, vs = jobs.vs, C = jb.C;
+  const int n = blockIdx.x * TL_BN + wave * 16 + l15;
+  const bool ok = n < jobs.n;
+
+  // matrix tile i: columns j0.. of matrix i / n_jt; the loads of the next one
+  // are in flight while a tile is multiplied
+  const int n_jt = (vs + TL_BJ - 1) / TL_BJ, n_tiles = n_jt * jb.n_mats;
+  constexpr int PIECES = TL_BJ * KC / 8 / (64 * TL_NW);  // 16-byte pieces a thread
+  static_assert(PIECES >= 1 && TL_BJ * KC % (8 * 64 * TL_NW) == 0, "staging map");
+  constexpr int NP = PIECES;
+  uint32_t w[NP][4];
+  auto load = [&](int i) {
+    const TableLiftMat& t = jb.mat[i / n_jt];
+    const int j0 = (i % n_jt) * TL_BJ;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int e = p * 64 * TL_NW + tid;
+      w[p][0] = w[p][1] = w[p][2] = w[p][3] = 0;
+      if (t.vec == 2) {  // 8 outputs of one column
+        const int c = e / (TL_BJ / 8), j = j0 + e % (TL_BJ / 8) * 8;
+        if (c < C && j < ds) {  // ds is a multiple of 8
+          const uint4 u = *reinterpret_cast<const uint4*>(t.m + static_cast<size_t>(c) * t.m_cs + j);
+          w[p][0] = u.x; w[p][1] = u.y; w[p][2] = u.z; w[p][3] = u.w;
+        }
+      } else {  // 8 columns of one output
+        const int j = j0 + e / (KC / 8), c = e % (KC / 8) * 8;
+        if (j >= ds) continue;
+        if (t.vec == 1) {  // C is a multiple of 8
+          if (c < C) {
+            const uint4 u = *reinterpret_cast<const uint4*>(t.m + static_cast<size_t>(j) * t.m_rs + c);
+            w[p][0] = u.x; w[p][1] = u.y; w[p][2] = u.z; w[p][3] = u.w;
+          }
+        } else {
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            if (c + q < C)
+              w[p][q >> 1] |= static_cast<uint32_t>(t.m[static_cast<size_t>(j) * t.m_rs + static_cast<size_t>(c + q) * t.m_cs]) << (16 * (q & 1));
+        }
+      }
+    }
+  };
+  auto store = [&](int i) {
+    uint16_t* dst = s_m[i & 1];
+    const int vec = jb.mat[i / n_jt].vec;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int e = p * 64 * TL_NW + tid;
+      if (vec == 2) {
+        const int c = e / (TL_BJ / 8), j = e % (TL_BJ / 8) * 8;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) dst[(j + q) * ROW + c] = static_cast<uint16_t>(w[p][q >> 1] >> (16 * (q & 1)));
+      } else {
+        const int j = e / (KC / 8), c = e % (KC / 8) * 8;
+        *reinterpret_cast<uint4*>(dst + j * ROW + c) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+      }
+    }
+  };
+
+  load(0);
+  // the wave's 16 inputs, lane: columns 32 kk + 8 (lane / 16) .. + 7 of its token
+  bf16x8 x[3][NK];
+  const float* src = jb.in + static_cast<size_t>(ok ? n : 0) * C;
+  const bool vec_in = (C & 7) == 0 && (reinterpret_cast<uintptr_t>(jb.in) & 15u) == 0;
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk) {
+    const int c = kk * 32 + (lane >> 4) * 8;
+    float f[8];
+    if (vec_in) {
+      const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+      const float4 f0 = c < C ? *reinterpret_cast<const float4*>(src + c) : z;
+      const float4 f1 = c < C ? *reinterpret_cast<const float4*>(src + c + 4) : z;
+      f[0] = f0.x; f[1] = f0.y; f[2] = f0.z; f[3] = f0.w;
+      f[4] = f1.x; f[5] = f1.y; f[6] = f1.z; f[7] = f1.w;
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) f[q] = c + q < C ? src[c + q] : 0.f;
+    }
+    union { uint16_t h[8]; bf16x8 v; } p0, p1, p2;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      p0.h[q] = bf16_rne(f[q]);
+      const float r1 = f[q] - bf16_to_f32(p0.h[q]);
+      p1.h[q] = bf16_rne(r1);
+      p2.h[q] = bf16_rne(r1 - bf16_to_f32(p1.h[q]));
+    }
+    x[0][kk] = p0.v;
+    x[1][kk] = p1.v;
+    x[2][kk] = p2.v;
+  }
+  store(0);
+  __syncthreads();
+  for (int i = 0; i < n_tiles; ++i) {
+    if (i + 1 < n_tiles) load(i + 1);
+    const uint16_t* sm = s_m[i & 1];
+    floatx4 acc[TL_BJ / 16];
+#pragma unroll
+    for (int a = 0; a < TL_BJ / 16; ++a) acc[a] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk)
+#pragma unroll
+      for (int a = 0; a < TL_BJ / 16; ++a) {
+        const bf16x8 m = *reinterpret_cast<const bf16x8*>(sm + (a * 16 + l15) * ROW + kk * 32 + (lane >> 4) * 8);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) acc[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, x[t][kk], acc[a], 0, 0, 0);
+      }
+    // buffer (i + 1) & 1 was last read before the barrier that ended tile i - 1
+    if (i + 1 < n_tiles) store(i + 1);
+    __syncthreads();
+    // lane: outputs 16 a + 4 (lane / 16) + q of its token; zero past d_state
+    if (ok) {
+      float* o = jb.mat[i / n_jt].out + static_cast<size_t>(n) * vs;
+      const int jq = (i % n_jt) * TL_BJ + (lane >> 4) * 4;
+#pragma unroll
+      for (int a = 0; a < TL_BJ / 16; ++a) {
+        const int j = jq + a * 16;
+        // the padding is zero whatever the input holds (0 * infinity is not)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[a][q] = j + q < ds ? acc[a][q] : 0.f;
+        if ((vs & 3) == 0) {
+          if (j < vs) __builtin_nontemporal_store(acc[a], reinterpret_cast<floatx4*>(o + j));
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (j + q < vs) o[j + q] = acc[a][q];
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // slice_sum: in-place, in-order sum of the split-K slices into slice 0.
 // ---------------------------------------------------------------------------
 struct SliceArr {
@@ -1612,30 +1937,33 @@ void launch_corrector_prepare(const brisk_corrector& c, const uint16_t* lm_head,
   const size_t vsz = step_vec_stride(ds);
   float* PE = static_cast<float*>(ws);
   float* PC = PE + static_cast<size_t>(V) * c.d_tproj;
-  ProjJobs pj{};
+  TableProjJobs pj{};
   pj.d = d;
-  pj.splits = 1;
-  pj.job[0] = ProjJob{tok_embed, nullptr, V, c.d_tproj, V, c.P_e, PE, static_cast<size_t>(V) * c.d_tproj};
-  pj.job[2] = ProjJob{lm_head, nullptr, V, c.rank, V, c.W_c, PC, static_cast<size_t>(V) * c.rank};
-  int gx = 0;
-  for (int j = 0; j < kMaxProjJobs; ++j) gx = std::max(gx, proj_tiles(pj.job[j].n, pj.job[j].J, 128));
-  hipLaunchKernelGGL(gather_proj_kernel<128>, dim3(gx, kMaxProjJobs + 1, 1), dim3(256), 0, s, pj);
+  pj.job[0] = TableProjJob{tok_embed, c.P_e, PE, V, c.d_tproj};
+  pj.job[1] = TableProjJob{lm_head, c.W_c, PC, V, c.rank};
+  const int jt = (std::max(c.d_tproj, c.rank) + TP_BJ - 1) / TP_BJ;
+  hipLaunchKernelGGL(table_proj_kernel, dim3(256, jt), dim3(64 * TP_NW), 0, s, pj);
 
-  auto fterm = [&](const float* in, int C, const uint16_t* m, int m_rs, int m_cs) {
-    const bool a16 = (reinterpret_cast<uintptr_t>(in) & 15u) == 0 && C % 16 == 0;
-    const bool m16 = (reinterpret_cast<uintptr_t>(m) & 15u) == 0 &&
-                     (m_cs == 1 ? m_rs % 8 == 0 && C % 16 == 0 : m_rs == 1 && m_cs % 8 == 0 && ds % 16 == 0);
-    return LiftTerm{in, 0, C, 1, 0, C, m, m_rs, m_cs, a16 ? 1 : 0, m16 ? 1 : 0};
+  // runs of 8 along c (rows of W_z and W_h) or along j (rows of W_s)
+  auto mat = [&](const uint16_t* m, int m_rs, int m_cs, int C, float* out) {
+    const bool a16 = (reinterpret_cast<uintptr_t>(m) & 15u) == 0;
+    const int vec = !a16 ? 0 : m_cs == 1 ? (m_rs % 8 == 0 && C % 8 == 0 ? 1 : 0) : (m_cs % 8 == 0 && ds % 8 == 0 ? 2 : 0);
+    return TableLiftMat{m, m_rs, m_cs, vec, out};
   };
-  const LiftTerm none{nullptr, 0, 0, 0, 0, 0, nullptr, 0, 0, 0, 0};
   const size_t tstride = static_cast<size_t>(V) * vsz;
-  LiftJobs lj{};
+  TableLiftJobs lj{};
+  lj.n = V;
   lj.ds = ds;
-  lj.job[0] = LiftJob{{fterm(PC, c.rank, c.W_s, 1, ds), none}, V, tables, 1, vsz, vsz};
-  lj.job[1] = LiftJob{{fterm(PE, c.d_tproj, c.W_z + tp_off, d_in, 1), none}, V, tables + tstride, 1, vsz, vsz};
-  lj.job[2] = LiftJob{{fterm(PE, c.d_tproj, c.W_h + tp_off, d_in, 1), none}, V, tables + 2 * tstride, 1, vsz, vsz};
-  const dim3 grid((V + LT_BN - 1) / LT_BN, static_cast<int>((vsz + LT_BJ - 1) / LT_BJ), kMaxLiftJobs);
-  hipLaunchKernelGGL(lift_kernel<1>, grid, dim3(256), 0, s, lj);
+  lj.vs = static_cast<int>(vsz);
+  lj.job[0] = TableLiftJob{PC, c.rank, 1, {mat(c.W_s, 1, ds, c.rank, tables), {}}};
+  lj.job[1] = TableLiftJob{PE, c.d_tproj, 2,
+                           {mat(c.W_z + tp_off, d_in, 1, c.d_tproj, tables + tstride),
+                            mat(c.W_h + tp_off, d_in, 1, c.d_tproj, tables + 2 * tstride)}};
+  const int cmax = std::max(c.d_tproj, c.rank);
+  const dim3 grid((V + TL_BN - 1) / TL_BN, 2), blk(64 * TL_NW);
+  if (cmax <= 64) hipLaunchKernelGGL(table_lift_kernel<2>, grid, blk, 0, s, lj);
+  else if (cmax <= 128) hipLaunchKernelGGL(table_lift_kernel<4>, grid, blk, 0, s, lj);
+  else hipLaunchKernelGGL(table_lift_kernel<8>, grid, blk, 0, s, lj);
 }
 
 }  // namespace brisk
