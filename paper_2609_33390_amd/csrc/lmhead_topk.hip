@@ -270,7 +270,13 @@ __device__ __forceinline__ bool is_candidate_reg(const int (&ids)[N], uint64_t m
 
 // One workgroup per compute unit (the LDS footprint allows no more), so the
 // compiler may split the whole register file among the workgroup's waves.
-template <class C, int KP, bool SAMPLE = false>
+// STREAM: one row tile, so every lm_head row is read by one workgroup only.
+// Its copies are then non-temporal, which leaves the L2 to the hidden rows
+// that all workgroups re-read: 32 rows 175 -> 168 us, 64 rows 198 -> 187, 96
+// rows 190 -> 182, 256 rows 281 -> 272 (126464 x 4096).  Rows that several
+// workgroups read are better kept (512 rows 476 -> 477, 4096 rows 3234 ->
+// 3470 us).
+template <class C, int KP, bool SAMPLE = false, bool STREAM = false>
 __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA / 256, C::NTA / 256))) void lmhead_topk_kernel(
     const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, int rows, int d, int V,
     int n_rtiles, int n_groups, int tiles_per_group, int even, uint64_t* __restrict__ partial,
@@ -357,7 +363,7 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
       const unsigned lv = lane_voff_of(j);
       if (j * C::RPI < C::BV) {
         const unsigned off = lv + (v0 + static_cast<unsigned>(j * C::RPI)) * row_bytes + k0b;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr_t)(base + j * 1024), 16, off, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr_t)(base + j * 1024), 16, off, 0, 0, STREAM ? 2 : 0);
       } else {
         const unsigned off = lv + static_cast<unsigned>(r0 + j * C::RPI - C::BV) * row_bytes + k0b;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rh, (lds_ptr_t)(base + j * 1024), 16, off, 0, 0, 0);
@@ -1165,12 +1171,20 @@ Plan make_plan(int rows, int V, int K, bool sample = false) {
   return c4 <= c2 && c4 <= c3 ? p4 : (c3 <= c2 ? p3 : p2);
 }
 
+template <class C, int KP, bool SAMPLE, bool STREAM>
+void launch_tile_as(const Plan& p, const uint16_t* H, const uint16_t* W, int rows, int d, int V,
+                    uint64_t* partial, hipStream_t s, const SampleArgs& sa) {
+  const int nblocks = p.n_rtiles * p.n_groups;
+  hipLaunchKernelGGL((lmhead_topk_kernel<C, KP, SAMPLE, STREAM>), dim3(nblocks), dim3(C::NTA), 0, s, H, W, rows,
+                     d, V, p.n_rtiles, p.n_groups, p.tiles_per_group, p.even, partial, p.n_parts, sa);
+}
+
 template <class C, int KP, bool SAMPLE = false>
 void launch_tile(const Plan& p, const uint16_t* H, const uint16_t* W, int rows, int d, int V,
                  uint64_t* partial, hipStream_t s, SampleArgs sa = SampleArgs{}) {
-  const int nblocks = p.n_rtiles * p.n_groups;
-  hipLaunchKernelGGL((lmhead_topk_kernel<C, KP, SAMPLE>), dim3(nblocks), dim3(C::NTA), 0, s, H, W, rows,
-                     d, V, p.n_rtiles, p.n_groups, p.tiles_per_group, p.even, partial, p.n_parts, sa);
+  // up to 64 rows there is one row tile
+  if (C::BR <= 64 || p.n_rtiles == 1) launch_tile_as<C, KP, SAMPLE, true>(p, H, W, rows, d, V, partial, s, sa);
+  else if constexpr (C::BR > 64) launch_tile_as<C, KP, SAMPLE, false>(p, H, W, rows, d, V, partial, s, sa);
 }
 
 // ---------------------------------------------------------------------------
