@@ -21,7 +21,7 @@ SOURCES = ["lmhead_topk.hip", "corrector.hip", "verify.hip", "profile.hip", "los
 ARCH = "gfx950"
 # Packed-fp32 instructions stay off: the compiler must not form them itself.
 GPU_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-COMMON = ["-O3", "-fPIC", "-std=c++17", f"--offload-arch={ARCH}", "-Wall",
+COMMON = ["-O3", "-fPIC", "-std=c++20", f"--offload-arch={ARCH}", "-Wall",
           "-Wno-unused-function", "-I", os.path.join(ROOT, "include")]
 
 

@@ -561,7 +561,6 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
     for (int a = 0; a < C::TV; ++a)
 #pragma unroll
       for (int b = 0; b < C::TR; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-    int kt0 = 0;
     if constexpr (C::PINGPONG) {
       // The two waves of a SIMD (w and w + 4: wr = 0 and 1) take turns: while
       // one runs the 32 products of a 32-wide step, the other reads its next
@@ -577,13 +576,11 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
       // first phase refills the buffer of slice g - 1, which the other group
       // finished reading in phase 4g - 1 at the latest; both groups' copies
       // have landed by the end of phase 4g + 3, before slice g + 1 is read.
-      // The last slice of a ragged d, which needs zeroing, runs in the plain
-      // loop below.
-      kt0 = tail ? nk - 1 : nk;
       stage_sync<0>();
       if (wr == 1) phase_end();
-      for (int kt = 0; kt < kt0; ++kt) {
-        const int g = tl * nk + kt;
+      // RAGGED: the last slice of a ragged d, whose chunks past d hold other
+      // data; the lm_head operand is zeroed there
+      auto slice = [&]<bool RAGGED>(int g) {
         const unsigned char* sb = smem + (g % C::STAGES) * C::STAGE_BYTES;
         bf16x8 b[C::TR], a[C::TV];
         issue(g + 1);
@@ -591,6 +588,11 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
           read_frags(sb, kk, a, b);
+          if constexpr (RAGGED) {
+#pragma unroll
+            for (int x = 0; x < C::TV; ++x)
+              if (kk * 4 + (lane >> 4) >= tail) a[x] = bf16x8{};
+          }
           if (kk == 1 && wr == 1) vm_wait();
           lds_wait();
           phase_end();
@@ -598,10 +600,14 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
           if (kk == 1 && wr == 0) vm_wait();
           phase_end();
         }
-      }
+      };
+      const int nfull = tail ? nk - 1 : nk;
+      for (int kt = 0; kt < nfull; ++kt) slice.template operator()<false>(tl * nk + kt);
+      if (tail) slice.template operator()<true>(tl * nk + nk - 1);
       if (wr == 0) phase_end();
+      return;
     }
-    for (int kt = kt0; kt < nk; ++kt) {
+    for (int kt = 0; kt < nk; ++kt) {
       const int g = tl * nk + kt;
       // slice g landed; everyone is done with slice g-1 (in the last slices
       // fewer younger copies exist, so wait for all)
@@ -1132,14 +1138,16 @@ Plan make_plan_for(int cfg, int rows, int V, int K, int target = kTargetWorkgrou
   want = want < 1 ? 1 : (want > p.n_vtiles ? p.n_vtiles : want);
   p.tiles_per_group = (p.n_vtiles + want - 1) / want;
   p.n_groups = (p.n_vtiles + p.tiles_per_group - 1) / p.tiles_per_group;
-  // When runs of whole tiles leave compute units idle, cut the vocabulary
-  // into one equal share per compute unit instead (the partly masked last
-  // tile costs MFMA time but no memory traffic).  Lists longer than kFiltKeys
-  // keep whole tiles on the 256-row tile: more shares would mean more key
-  // lists, past the no-alloc scratch for shapes that fit it.
+  // Weight-streaming shapes: when runs of whole tiles leave compute units
+  // idle, cut the vocabulary into one equal share per compute unit instead
+  // (the partly masked last tile costs MFMA time, which these shapes have to
+  // spare, but no memory traffic).  On the larger tiles a partial tile takes
+  // the time of a whole one, and more workgroups only contend for the L2
+  // (248 rows x 152064 tokens, d = 1920: 3 tiles each on 198 workgroups 196
+  // us, on 256 with shares 208 us).
   const int want_all = target / p.n_rtiles < 1 ? 1 : target / p.n_rtiles;
   p.even = 0;
-  if ((p.KP <= kFiltKeys || C::WAVES_R == 1) && p.n_groups < want_all && V / want_all >= C::BV / 2) {
+  if (!C::PINGPONG && !(C::WAVES_R == 2 && p.n_rtiles > 1) && p.n_groups < want_all && V / want_all >= C::BV / 2) {
     p.even = 1;
     p.n_groups = want_all;
     p.tiles_per_group = (V / want_all + 16 + C::BV - 1) / C::BV;
@@ -1149,8 +1157,9 @@ Plan make_plan_for(int cfg, int rows, int V, int K, int target = kTargetWorkgrou
 }
 
 // Time of a pass in arbitrary units: the tiles of the longest share times the
-// tile's time per reduction slice.  4096 rows x 126464 tokens took 1.00, 1.47
-// and 1.69 us a slice on the 128-, 192- and 256-row tiles.
+// tile's time.  Relative to the 256-row tile, a tile takes 0.94 of the time
+// with 192 rows (4 tiles each at 384 rows: 432 against 459 us) and 0.63-0.65
+// with 128 (546 rows x 100277 tokens: 8 tiles 370, 5 tiles 368 us).
 int plan_cost(const Plan& p, int V, int slice) {
   const int share = (V + p.n_groups - 1) / p.n_groups;
   return (p.even ? (share + 255) / 256 : p.tiles_per_group) * slice;
@@ -1167,7 +1176,7 @@ Plan make_plan(int rows, int V, int K, bool sample = false) {
   // 493, 768 rows 811 / 783 / 707, 4096 rows 3974 / 4221 / 3352.
   const Plan p2 = make_plan_for<Rows128>(2, rows, V, K), p3 = make_plan_for<Rows192>(3, rows, V, K),
              p4 = make_plan_for<Rows256>(4, rows, V, K);
-  const int c2 = plan_cost(p2, V, 20), c3 = plan_cost(p3, V, 29), c4 = plan_cost(p4, V, 34);
+  const int c2 = plan_cost(p2, V, 22), c3 = plan_cost(p3, V, 32), c4 = plan_cost(p4, V, 34);
   return c4 <= c2 && c4 <= c3 ? p4 : (c3 <= c2 ? p3 : p2);
 }
 
@@ -1182,9 +1191,12 @@ void launch_tile_as(const Plan& p, const uint16_t* H, const uint16_t* W, int row
 template <class C, int KP, bool SAMPLE = false>
 void launch_tile(const Plan& p, const uint16_t* H, const uint16_t* W, int rows, int d, int V,
                  uint64_t* partial, hipStream_t s, SampleArgs sa = SampleArgs{}) {
-  // up to 64 rows there is one row tile
-  if (C::BR <= 64 || p.n_rtiles == 1) launch_tile_as<C, KP, SAMPLE, true>(p, H, W, rows, d, V, partial, s, sa);
-  else if constexpr (C::BR > 64) launch_tile_as<C, KP, SAMPLE, false>(p, H, W, rows, d, V, partial, s, sa);
+  // lm_head rows that are not whole 128-byte lines share lines between
+  // neighbouring slices, which must stay in L2 (248 rows x 131072 tokens, d =
+  // 1896: 196 us non-temporal, 176 not)
+  const bool lines = d % 64 == 0 && (reinterpret_cast<uintptr_t>(W) & 127u) == 0;
+  if (p.n_rtiles == 1 && lines) launch_tile_as<C, KP, SAMPLE, true>(p, H, W, rows, d, V, partial, s, sa);
+  else launch_tile_as<C, KP, SAMPLE, false>(p, H, W, rows, d, V, partial, s, sa);
 }
 
 // ---------------------------------------------------------------------------
