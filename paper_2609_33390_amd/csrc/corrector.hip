@@ -59,18 +59,17 @@ struct FillArgs {
   const int32_t* cand_id;
   const int32_t* anchor;
   float* SB;             // [rows][2 + 3K][vs]
-  float* TZA;            // [B][ds]
+  float* TZA;            // [B][vs]
   float* THA;
-  int rows, K, B, V, ds, vs;  // rows = B = 0: nothing to copy
+  int rows, K, B, V, vs;  // rows = B = 0: nothing to copy
 };
 
 // Vector n: the candidates' EH, TZ and TH rows first, then the anchors' TZ
-// and TH rows.  fill_id gives its token id; fill_vec its source, destination
-// and length for that id.
+// and TH rows.  fill_id gives its token id; fill_vec its source and
+// destination for that id.
 struct FillVec {
   const float* src;
   float* dst;
-  int len;
 };
 __device__ __forceinline__ int fill_id(const FillArgs& a, int n) {
   const int n_cand = a.rows * 3 * a.K;
@@ -85,20 +84,17 @@ __device__ __forceinline__ FillVec fill_vec(const FillArgs& a, int n, int v) {
   if (n < n_cand) {
     const int r = n / (3 * a.K), f = n % (3 * a.K), kind = f / a.K;
     return {a.tables + (static_cast<size_t>(kind) * a.V + v) * a.vs,
-            a.SB + (static_cast<size_t>(r) * (2 + 3 * a.K) + 2 + f) * a.vs, a.vs};
+            a.SB + (static_cast<size_t>(r) * (2 + 3 * a.K) + 2 + f) * a.vs};
   }
   const int m = n - n_cand, b = m % a.B, kind = 1 + m / a.B;  // TZ, then TH
   return {a.tables + (static_cast<size_t>(kind) * a.V + v) * a.vs,
-          (kind == 1 ? a.TZA : a.THA) + static_cast<size_t>(b) * a.ds, a.ds};
+          (kind == 1 ? a.TZA : a.THA) + static_cast<size_t>(b) * a.vs};
 }
 
-// A wavefront copies kFillBatch consecutive vectors at a time: lane g loads
-// vector g's token id (one load for the batch), then every lane loads its 16
-// bytes of each source row before the first store, so the batch waits for
-// two memory latencies instead of two per vector.  With 256-float table rows
-// (d_state <= 256) the row loads are unconditional (a table row is never
-// shorter) and only the stores into rows of d_state floats are masked; other
-// strides copy vector by vector.
+// A wavefront copies kFillBatch consecutive vectors of 256 floats at a time:
+// lane g loads vector g's token id (one load for the batch), then every lane
+// loads its 16 bytes of each source row before the first store, so the batch
+// waits for two memory latencies instead of two per vector.
 constexpr int kFillBatch = 4;
 __device__ void fill_rows(const FillArgs& a, int first, int step) {
   const int lane = threadIdx.x & 63;
@@ -106,33 +102,21 @@ __device__ void fill_rows(const FillArgs& a, int first, int step) {
   // the batch index is wave-uniform
   for (int n0 = __builtin_amdgcn_readfirstlane(first * kFillBatch); n0 < n_all; n0 += step * kFillBatch) {
     const int my_id = fill_id(a, min(n0 + min(lane, kFillBatch - 1), n_all - 1));
-    if (a.vs == 256 && (a.ds & 3) == 0) {
-      // named, not arrays, so that nothing is staged through memory; a batch
-      // past the last vector repeats it (the same bytes to the same place)
-      static_assert(kFillBatch == 4, "the batch below is written out for four vectors");
-      const FillVec f0 = fill_vec(a, min(n0 + 0, n_all - 1), __builtin_amdgcn_readlane(my_id, 0));
-      const FillVec f1 = fill_vec(a, min(n0 + 1, n_all - 1), __builtin_amdgcn_readlane(my_id, 1));
-      const FillVec f2 = fill_vec(a, min(n0 + 2, n_all - 1), __builtin_amdgcn_readlane(my_id, 2));
-      const FillVec f3 = fill_vec(a, min(n0 + 3, n_all - 1), __builtin_amdgcn_readlane(my_id, 3));
-      const float4 v0 = *reinterpret_cast<const float4*>(f0.src + lane * 4);
-      const float4 v1 = *reinterpret_cast<const float4*>(f1.src + lane * 4);
-      const float4 v2 = *reinterpret_cast<const float4*>(f2.src + lane * 4);
-      const float4 v3 = *reinterpret_cast<const float4*>(f3.src + lane * 4);
-      if (lane * 4 < f0.len) *reinterpret_cast<float4*>(f0.dst + lane * 4) = v0;
-      if (lane * 4 < f1.len) *reinterpret_cast<float4*>(f1.dst + lane * 4) = v1;
-      if (lane * 4 < f2.len) *reinterpret_cast<float4*>(f2.dst + lane * 4) = v2;
-      if (lane * 4 < f3.len) *reinterpret_cast<float4*>(f3.dst + lane * 4) = v3;
-      continue;
-    }
-    for (int g = 0; g < kFillBatch && n0 + g < n_all; ++g) {
-      const FillVec f = fill_vec(a, n0 + g, __builtin_amdgcn_readlane(my_id, g));
-      if ((f.len & 3) == 0) {
-        for (int e = lane * 4; e < f.len; e += 256)
-          *reinterpret_cast<float4*>(f.dst + e) = *reinterpret_cast<const float4*>(f.src + e);
-      } else {
-        for (int e = lane; e < f.len; e += 64) f.dst[e] = f.src[e];
-      }
-    }
+    // named, not arrays, so that nothing is staged through memory; a batch
+    // past the last vector repeats it (the same bytes to the same place)
+    static_assert(kFillBatch == 4, "the batch below is written out for four vectors");
+    const FillVec f0 = fill_vec(a, min(n0 + 0, n_all - 1), __builtin_amdgcn_readlane(my_id, 0));
+    const FillVec f1 = fill_vec(a, min(n0 + 1, n_all - 1), __builtin_amdgcn_readlane(my_id, 1));
+    const FillVec f2 = fill_vec(a, min(n0 + 2, n_all - 1), __builtin_amdgcn_readlane(my_id, 2));
+    const FillVec f3 = fill_vec(a, min(n0 + 3, n_all - 1), __builtin_amdgcn_readlane(my_id, 3));
+    const float4 v0 = *reinterpret_cast<const float4*>(f0.src + lane * 4);
+    const float4 v1 = *reinterpret_cast<const float4*>(f1.src + lane * 4);
+    const float4 v2 = *reinterpret_cast<const float4*>(f2.src + lane * 4);
+    const float4 v3 = *reinterpret_cast<const float4*>(f3.src + lane * 4);
+    *reinterpret_cast<float4*>(f0.dst + lane * 4) = v0;
+    *reinterpret_cast<float4*>(f1.dst + lane * 4) = v1;
+    *reinterpret_cast<float4*>(f2.dst + lane * 4) = v2;
+    *reinterpret_cast<float4*>(f3.dst + lane * 4) = v3;
   }
 }
 
@@ -1016,6 +1000,155 @@ __global__ __launch_bounds__(256) void slice_sum_kernel(SliceArrs sa) {
 }
 
 // ---------------------------------------------------------------------------
+// gate: the minGRU step of every row for every token that may precede it.
+//
+// z and the candidate state of row n depend on the token selected at row
+// n - 1, not on the state, so they are known for all K candidates of row n - 1
+// before the scan starts: a = 1 - z and b = z h~ replace what the candidate
+// feeds into row n (TZ_k and TH_k of row n - 1), and u_n = a u_{n-1} + b is all
+// that is left of the update in the scan.  The selection gate's pre-activation
+// without its state part replaces the cross logit.  The anchors take the same
+// way into the first row of their block.
+//
+// The recurrence is one wavefront that is bound by its instructions, this is a
+// parallel pass: K times the sigmoids, but at 16 x 32 rows, K = 16, the scan
+// went from 42 to 28.5 us and at 1 x 32, K = 8, from 24.4 to 18.3.  With the
+// per-token tables it also copies the candidates' EH rows into the step
+// blocks, in place of a copy of the table rows (9.6 us at 16 x 32, K = 16;
+// this pass 12-13 us, bound by those rows).
+//
+// One wavefront per row and pair of candidates, or per anchor.
+// ---------------------------------------------------------------------------
+constexpr int kGateGroup = 2;
+struct GateArgs {
+  const float* tables;   // [3][V][vs] EH, TZ, TH by token id, or null: TZ and TH are in the step blocks
+  const int32_t* cand_id;
+  const int32_t* anchor;
+  const float* cand_logit;
+  float* SB;             // [rows][2 + 3K][vs]
+  float* TZA;            // [B][vs] anchors: TZ in (without tables), a out
+  float* THA;            //         TH in, b out
+  float* X;              // [rows * K + B] cross logits in, gate terms out
+  const float* FZ;       // [5][vs]
+  const float* FH;
+  const uint16_t* w_g;
+  float b_g;
+  int B, L, K, V, ds, vs;
+};
+
+__device__ __forceinline__ float sigmoid_rcp(float x) {
+  return __builtin_amdgcn_rcpf(1.0f + __expf(-x));
+}
+
+// W = 4: vectors of 16 bytes (vs a multiple of 4), else single floats
+template <int W>
+__global__ __launch_bounds__(256) void gate_kernel(GateArgs a) {
+  typedef float vec __attribute__((ext_vector_type(W)));
+  const int lane = threadIdx.x & 63;
+  const int rows = a.B * a.L, K = a.K, F = 2 + 3 * K, vs = a.vs, ds = a.ds;
+  const int ng = (K + kGateGroup - 1) / kGateGroup;
+  const int it = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  if (it >= rows * ng + a.B) return;
+  const bool is_anchor = it >= rows * ng;
+  // the row whose candidates these are (anchors: none), and the row they step into
+  const int b = is_anchor ? it - rows * ng : 0;
+  const int r = is_anchor ? -1 : it / ng, k0 = is_anchor ? 0 : it % ng * kGateGroup;
+  const int nk = is_anchor ? 1 : min(kGateGroup, K - k0);
+  const int n = is_anchor ? b * a.L : r + 1;
+  const bool step = is_anchor || n % a.L != 0;  // the last row of a block steps into none
+  int tok[kGateGroup];
+#pragma unroll
+  for (int q = 0; q < kGateGroup; ++q)
+    tok[q] = is_anchor ? a.anchor[b] : a.cand_id[static_cast<size_t>(r) * K + k0 + min(q, nk - 1)];
+  // row n's features: 0, 1 and the logit half of 4 depend on the row alone
+  float p0 = 0.f, p1 = 0.f, c0 = 0.f, phi2[kGateGroup], phi3[kGateGroup], xq[kGateGroup], gate[kGateGroup];
+  float* x = is_anchor ? a.X + static_cast<size_t>(rows) * K + b : a.X + static_cast<size_t>(r) * K + k0;
+  if (step) {
+    const float* cl = a.cand_logit + static_cast<size_t>(n) * K;
+    const int32_t* ci = a.cand_id + static_cast<size_t>(n) * K;
+    c0 = cl[0];
+    p0 = c0 - cl[1];
+    p1 = c0 - cl[3];
+    const int i0 = ci[0], i1 = ci[1], i2 = ci[2], i3 = ci[3];
+    float wphi[5];
+#pragma unroll
+    for (int f = 0; f < 5; ++f) wphi[f] = bf16_to_f32(a.w_g[ds + f]);
+    const float row = a.b_g + wphi[0] * p0 + wphi[1] * p1;
+#pragma unroll
+    for (int q = 0; q < kGateGroup; ++q) {
+      const int t = tok[q];
+      phi2[q] = t == i0 ? 1.f : 0.f;
+      phi3[q] = t == i0 || t == i1 || t == i2 || t == i3 ? 1.f : 0.f;
+      xq[q] = x[min(q, nk - 1)];
+      gate[q] = row + wphi[2] * phi2[q] + wphi[3] * phi3[q] + wphi[4] * (c0 - xq[q]);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kGateGroup; ++q) tok[q] = clamp_id(tok[q], a.V);
+  for (int e = lane * W; e < vs; e += 64 * W) {
+    // every load before the first store
+    vec tz[kGateGroup], th[kGateGroup], eh[kGateGroup], az, ah, fz[3], fh[3];
+    float* sb = a.SB + (is_anchor ? 0 : static_cast<size_t>(r) * F * vs) + e;
+#pragma unroll
+    for (int q = 0; q < kGateGroup; ++q) {
+      const int k = k0 + min(q, nk - 1);
+      if (a.tables) {
+        const float* t = a.tables + static_cast<size_t>(tok[q]) * vs + e;
+        const size_t kind = static_cast<size_t>(a.V) * vs;
+        if (!is_anchor) eh[q] = *reinterpret_cast<const vec*>(t);
+        tz[q] = *reinterpret_cast<const vec*>(t + kind);
+        th[q] = *reinterpret_cast<const vec*>(t + 2 * kind);
+      } else if (is_anchor) {
+        tz[q] = *reinterpret_cast<const vec*>(a.TZA + static_cast<size_t>(b) * vs + e);
+        th[q] = *reinterpret_cast<const vec*>(a.THA + static_cast<size_t>(b) * vs + e);
+      } else {
+        tz[q] = *reinterpret_cast<const vec*>(sb + static_cast<size_t>(2 + K + k) * vs);
+        th[q] = *reinterpret_cast<const vec*>(sb + static_cast<size_t>(2 + 2 * K + k) * vs);
+      }
+    }
+    if (step) {
+      const float* sn = a.SB + static_cast<size_t>(n) * F * vs + e;
+      az = *reinterpret_cast<const vec*>(sn);
+      ah = *reinterpret_cast<const vec*>(sn + vs);
+      auto feat = [&](const float* m, int f) { return *reinterpret_cast<const vec*>(m + static_cast<size_t>(f) * vs + e); };
+      az += feat(a.FZ, 0) * p0 + feat(a.FZ, 1) * p1;
+      ah += feat(a.FH, 0) * p0 + feat(a.FH, 1) * p1;
+#pragma unroll
+      for (int f = 0; f < 3; ++f) {
+        fz[f] = feat(a.FZ, 2 + f);
+        fh[f] = feat(a.FH, 2 + f);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kGateGroup; ++q) {
+      const int k = k0 + q;
+      if (a.tables && !is_anchor && q < nk) *reinterpret_cast<vec*>(sb + static_cast<size_t>(2 + k) * vs) = eh[q];
+      if (!step || q >= nk) continue;
+      vec oa, ob;
+#pragma unroll
+      for (int j = 0; j < W; ++j) {
+        const float p4 = c0 - xq[q];
+        const float gz = az[j] + tz[q][j] + fz[0][j] * phi2[q] + fz[1][j] * phi3[q] + fz[2][j] * p4;
+        const float gh = ah[j] + th[q][j] + fh[0][j] * phi2[q] + fh[1][j] * phi3[q] + fh[2][j] * p4;
+        const float z = sigmoid_rcp(gz);
+        const bool in = e + j < ds;  // the padding of the state stays zero
+        oa[j] = in ? 1.f - z : 0.f;
+        ob[j] = in ? z * gh : 0.f;
+      }
+      float* da = is_anchor ? a.TZA + static_cast<size_t>(b) * vs + e : sb + static_cast<size_t>(2 + K + k) * vs;
+      float* db = is_anchor ? a.THA + static_cast<size_t>(b) * vs + e : sb + static_cast<size_t>(2 + 2 * K + k) * vs;
+      *reinterpret_cast<vec*>(da) = oa;
+      *reinterpret_cast<vec*>(db) = ob;
+    }
+  }
+  if (step && lane == 0) {
+#pragma unroll
+    for (int q = 0; q < kGateGroup; ++q)
+      if (q < nk) x[q] = gate[q];
+  }
+}
+
+// ---------------------------------------------------------------------------
 // scan: one workgroup per sequence, one 64-wide slice of the state per wave.
 //
 // The lift kernel leaves each row's step inputs in one contiguous "step
@@ -1042,8 +1175,8 @@ struct ScanArgs {
   const float* SB;   // [rows, F, ds] step blocks
   const float* TZA;  // [B, ds] anchor-token inputs of step 0
   const float* THA;
-  const float* FZ;   // [5, ds] W_z[:, feat] P_phi
-  const float* FH;   // [5, ds] W_h[:, feat] P_phi
+  const float* FZ;   // [5, vs] W_z[:, feat] P_phi
+  const float* FH;   // [5, vs] W_h[:, feat] P_phi
   const uint16_t* w_g;
   float alpha, b_g;
   const float* cand_logit;
@@ -1068,9 +1201,8 @@ struct ScanArgs {
 
 template <int KM>
 struct StepData {
-  float az, ah;
   float eh[KM];
-  float tz[KM], th[KM];
+  float ga[KM], gb[KM];  // what candidate k feeds into the next row: u = ga u + gb
   float cl, xs;
   int ci;
 };
@@ -1091,14 +1223,12 @@ __device__ __forceinline__ void load_step(StepData<KM>& s, const ScanArgs& a,
   const int F = 2 + 3 * a.K;
   const int vb = a.vs * 4;                // bytes per vector
   const int base = ii * F * vb;           // this row's step block inside the sequence
-  s.az = buf_ld(rsb, voff, base);
-  s.ah = buf_ld(rsb, voff, base + vb);
 #pragma unroll
   for (int k = 0; k < KM; ++k) {
     const int kk = k < a.K ? k : a.K - 1;
     s.eh[k] = buf_ld(rsb, voff, base + (2 + kk) * vb);
-    s.tz[k] = buf_ld(rsb, voff, base + (2 + a.K + kk) * vb);
-    s.th[k] = buf_ld(rsb, voff, base + (2 + 2 * a.K + kk) * vb);
+    s.ga[k] = buf_ld(rsb, voff, base + (2 + a.K + kk) * vb);
+    s.gb[k] = buf_ld(rsb, voff, base + (2 + 2 * a.K + kk) * vb);
   }
   const size_t nl = (static_cast<size_t>(b) * a.L + ii) * a.K + (lane < a.K ? lane : a.K - 1);
   s.cl = a.cand_logit[nl];
@@ -1131,26 +1261,17 @@ __global__ __launch_bounds__(512) void scan_kernel(ScanArgs a) {
       L * F * a.vs * 4, 0x00020000);
   const int voff = ec * 4;
 
-  float fz[5], fh[5];
   const float u0a = a.U0[static_cast<size_t>(b) * ds + ec];
   const float u0b = a.U0[static_cast<size_t>(a.B + b) * ds + ec];
   const float wg_e = bf16_to_f32(a.w_g[ec]);
-#pragma unroll
-  for (int f = 0; f < 5; ++f) {
-    fz[f] = a.FZ[f * ds + ec];
-    fh[f] = a.FH[f * ds + ec];
-  }
   float u = ok ? tanhf(u0a + u0b) : 0.f;
   const float wgu = ok ? wg_e : 0.f;
-  float wgphi[5];
-#pragma unroll
-  for (int f = 0; f < 5; ++f) wgphi[f] = bf16_to_f32(a.w_g[ds + f]);
   const float sig_alpha = sigmoidf_(a.alpha);
 
-  float prev_tz = a.TZA[static_cast<size_t>(b) * ds + ec];
-  float prev_th = a.THA[static_cast<size_t>(b) * ds + ec];
-  float prev_x = a.X[NC + b];
-  int prev_tok = a.anchor[b];
+  // what the token before row i feeds into it (gate_kernel)
+  float prev_a = a.TZA[static_cast<size_t>(b) * a.vs + ec];
+  float prev_b = a.THA[static_cast<size_t>(b) * a.vs + ec];
+  float prev_g = a.X[NC + b];
   const int my_v = lane < K ? lane : 0;  // the residual sum this lane assembles
 
   auto flush = [&](int i0, int n) {
@@ -1172,24 +1293,7 @@ __global__ __launch_bounds__(512) void scan_kernel(ScanArgs a) {
   };
 
   auto step = [&](const StepData<KM>& c, int i) {
-    const float c0 = readlane_f32(c.cl, 0), c1 = readlane_f32(c.cl, 1), c3 = readlane_f32(c.cl, 3);
-    const int id0 = __builtin_amdgcn_readlane(c.ci, 0);
-    const bool in4 = __ballot(lane < 4 && c.ci == prev_tok) != 0;
-    float phi[5];
-    phi[0] = c0 - c1;
-    phi[1] = c0 - c3;
-    phi[2] = prev_tok == id0 ? 1.f : 0.f;
-    phi[3] = in4 ? 1.f : 0.f;
-    phi[4] = c0 - prev_x;
-
-    float gz = c.az + prev_tz, gh = c.ah + prev_th;
-#pragma unroll
-    for (int f = 0; f < 5; ++f) {
-      gz += fz[f] * phi[f];
-      gh += fh[f] * phi[f];
-    }
-    const float z = sigmoidf_(gz);
-    u = ok ? (1.f - z) * u + z * gh : 0.f;
+    u = ok ? prev_a * u + prev_b : 0.f;
 
     float v[NV];
 #pragma unroll
@@ -1217,9 +1321,7 @@ __global__ __launch_bounds__(512) void scan_kernel(ScanArgs a) {
       my_d += (rd.x + rd.y) + (rd.z + rd.w);
       s += (rg.x + rg.y) + (rg.z + rg.w);
     }
-    s += a.b_g;
-#pragma unroll
-    for (int f = 0; f < 5; ++f) s += wgphi[f] * phi[f];
+    s += prev_g;
     const float g = sig_alpha * sigmoidf_(s);
     my_d = lane < K ? my_d : 0.f;
     const float lt = c.cl + g * my_d;
@@ -1238,16 +1340,15 @@ __global__ __launch_bounds__(512) void scan_kernel(ScanArgs a) {
         o_gam[t] = g;
       }
     }
-    float tz = c.tz[0], th = c.th[0];
+    float na = c.ga[0], nb = c.gb[0];
 #pragma unroll
     for (int k = 1; k < KM; ++k) {
-      tz = k == kstar ? c.tz[k] : tz;
-      th = k == kstar ? c.th[k] : th;
+      na = k == kstar ? c.ga[k] : na;
+      nb = k == kstar ? c.gb[k] : nb;
     }
-    prev_tz = tz;
-    prev_th = th;
-    prev_x = readlane_f32(c.xs, kstar);
-    prev_tok = sel;
+    prev_a = na;
+    prev_b = nb;
+    prev_g = readlane_f32(c.xs, kstar);
     if (t == kScanOutChunk - 1 || i == L - 1) flush(i - t, t + 1);
   };
 
@@ -1276,9 +1377,15 @@ __global__ __launch_bounds__(512) void scan_kernel(ScanArgs a) {
 // Step-block vectors are zero beyond d_state, so the padded state elements
 // stay zero without any masking in the loop.
 // ---------------------------------------------------------------------------
-template <int KM>
+// Where the step inputs come from: whole step blocks; AZ and AH from the step
+// blocks and the rest gathered from the per-token tables; or step blocks that
+// gate_kernel has turned into u = a u + b.
+enum class ScanIn { kBlocks, kGather, kGate };
+template <int KM, ScanIn IN>
 struct LdsStage {
-  static constexpr int NVEC = 2 + 3 * KM;       // AZ, AH, EH_k, TZ_k, TH_k
+  // AZ, AH, EH_k, TZ_k, TH_k; with kGate EH_k, a_k, b_k
+  static constexpr int V0 = IN == ScanIn::kGate ? 0 : 2;  // vector of EH_0
+  static constexpr int NVEC = V0 + 3 * KM;
   static constexpr int NDMA = NVEC + 3;         // + candidate logits, ids, cross logits
   static constexpr int FLOATS = NVEC * 256 + 3 * 64;
 };
@@ -1302,16 +1409,13 @@ __device__ __forceinline__ float dpp_rows(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWMASK, 0xF, false));
 }
 
-__device__ __forceinline__ float sigmoid_rcp(float x) {
-  return __builtin_amdgcn_rcpf(1.0f + __expf(-x));
-}
-
 // `ids` is the candidate-id array again, as a kernel argument of its own: read
 // only and unaliased, so the copy engine's wave-uniform reads of it become
 // scalar loads, which leave the vector-memory counter to the row copies.
-template <int KM, int D, bool TAB>
+template <int KM, int D, ScanIn IN>
 __global__ __launch_bounds__(128) void scan_pc_kernel(ScanArgs a, const int32_t* __restrict__ ids_in) {
-  using S = LdsStage<KM>;
+  using S = LdsStage<KM, IN>;
+  constexpr bool TAB = IN == ScanIn::kGather, GATE = IN == ScanIn::kGate;
   static_assert((D - 2) * S::NDMA <= 63, "vmcnt range");
   static_assert(2 * KM <= 62, "output lanes");
   __shared__ __align__(16) float ring[D * S::FLOATS];
@@ -1361,7 +1465,7 @@ __global__ __launch_bounds__(128) void scan_pc_kernel(ScanArgs a, const int32_t*
       if constexpr (tab) clamp_ids();
 #pragma unroll
       for (int v = 0; v < S::NVEC; ++v) {
-        if (tab && v >= 2) {
+        if constexpr (TAB) if (v >= 2) {
           // table kind (EH, TZ, TH) and candidate slot of vector v
           const int kind = (v - 2) / KM, k = (v - 2) % KM;
           const unsigned off = (static_cast<unsigned>(kind) * static_cast<unsigned>(a.V) +
@@ -1369,11 +1473,8 @@ __global__ __launch_bounds__(128) void scan_pc_kernel(ScanArgs a, const int32_t*
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rtb, (lds_vptr_t)(st + v * 256), 16, lane * 16, off, 0, 0);
           continue;
         }
-        int f;
-        if (v < 2) f = v;
-        else if (v < 2 + KM) f = 2 + min(v - 2, K - 1);
-        else if (v < 2 + 2 * KM) f = 2 + K + min(v - 2 - KM, K - 1);
-        else f = 2 + 2 * K + min(v - 2 - 2 * KM, K - 1);
+        const int w = v - S::V0;  // below 0: AZ and AH
+        const int f = w < 0 ? v : 2 + w / KM * K + min(w % KM, K - 1);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, (lds_vptr_t)(st + v * 256), 16, lane * 16,
                                                  rb + static_cast<unsigned>(f) * 1024u, 0, 0);
       }
@@ -1389,21 +1490,22 @@ __global__ __launch_bounds__(128) void scan_pc_kernel(ScanArgs a, const int32_t*
     // (a lane >= K, which nothing else reads).
     float cz[4][3], ch[4][3];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; !GATE && j < 4; ++j) {
       const bool ok = 4 * lane + j < ds;
       const int e = ok ? 4 * lane + j : ds - 1;
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
         const int f = q < 2 ? q : 4;
-        const float z = a.FZ[f * ds + e], h = a.FH[f * ds + e];
+        const float z = a.FZ[f * 256 + e], h = a.FH[f * 256 + e];
         cz[j][q] = ok ? z : 0.f;
         ch[j][q] = ok ? h : 0.f;
       }
     }
     float wphi[3];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) wphi[q] = bf16_to_f32(a.w_g[ds + (q < 2 ? q : 4)]);
+    for (int q = 0; !GATE && q < 3; ++q) wphi[q] = bf16_to_f32(a.w_g[ds + (q < 2 ? q : 4)]);
     auto prep = [&](int r) {
+      if constexpr (GATE) return;
       float* st = ring + (r % D) * S::FLOATS;
       f4_t* sv = reinterpret_cast<f4_t*>(st) + lane;
       float* sc = st + S::NVEC * 256;
@@ -1450,20 +1552,15 @@ __global__ __launch_bounds__(128) void scan_pc_kernel(ScanArgs a, const int32_t*
     const float u0b = a.U0[static_cast<size_t>(a.B + b) * ds + e];
     u[j] = ok ? tanhf(u0a + u0b) : 0.f;
     wgu[j] = ok ? bf16_to_f32(a.w_g[e]) : 0.f;
-    float tz, th;
-    if constexpr (TAB) {  // the anchor's rows of the TZ and TH tables
-      const size_t x0 = static_cast<size_t>(clamp_id(a.anchor[b], a.V));
-      tz = a.tables[(static_cast<size_t>(a.V) + x0) * 256 + e];
-      th = a.tables[(2 * static_cast<size_t>(a.V) + x0) * 256 + e];
-    } else {
-      tz = a.TZA[static_cast<size_t>(b) * ds + e];
-      th = a.THA[static_cast<size_t>(b) * ds + e];
-    }
+    // what the anchor feeds into the first row
+    const size_t x0 = TAB ? static_cast<size_t>(clamp_id(a.anchor[b], a.V)) : 0;
+    const float tz = TAB ? a.tables[(static_cast<size_t>(a.V) + x0) * 256 + e] : a.TZA[static_cast<size_t>(b) * 256 + e];
+    const float th = TAB ? a.tables[(2 * static_cast<size_t>(a.V) + x0) * 256 + e] : a.THA[static_cast<size_t>(b) * 256 + e];
     ptz[j] = ok ? tz : 0.f;
     pth[j] = ok ? th : 0.f;
 #pragma unroll
-    for (int f = 0; f < 5; ++f) {
-      const float z = a.FZ[f * ds + e], h = a.FH[f * ds + e];
+    for (int f = 0; !GATE && f < 5; ++f) {
+      const float z = a.FZ[f * 256 + e], h = a.FH[f * 256 + e];
       fz[j][f] = ok ? z : 0.f;
       fh[j][f] = ok ? h : 0.f;
     }
@@ -1472,6 +1569,7 @@ __global__ __launch_bounds__(128) void scan_pc_kernel(ScanArgs a, const int32_t*
 #pragma unroll
   for (int f = 0; f < 5; ++f) wgphi[f] = bf16_to_f32(a.w_g[ds + f]);
   const float sig_alpha = sigmoidf_(a.alpha);
+  // cross logit of the previous token, or (GATE) its gate term
   float prev_x = a.X[static_cast<size_t>(a.B) * L * K + b];
   int prev_tok = a.anchor[b];
 
@@ -1527,31 +1625,35 @@ __global__ __launch_bounds__(128) void scan_pc_kernel(ScanArgs a, const int32_t*
     const float* st = ring + (i % D) * S::FLOATS;
     const f4_t* sv = reinterpret_cast<const f4_t*>(st) + lane;  // vector v of the row at sv[64 v]
     const float* sc = st + S::NVEC * 256;                          // logits, ids, cross logits
-    const f4_t az = sv[0], ah = sv[64];
     f4_t eh[KM];
-#pragma unroll
-    for (int k = 0; k < KM; ++k) eh[k] = sv[64 * (2 + k)];
+    float phi2 = 0.f, phi3 = 0.f;
     const float cl_l = sc[lane], xs_l = sc[128 + lane], cl_mine = sc[my_cand];
     const int ci_l = __float_as_int(sc[64 + lane]);
-    const float s_row = sc[63];
-    int idu[4];
+    if constexpr (!GATE) {
+      const f4_t az = sv[0], ah = sv[64];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) idu[k] = __float_as_int(sc[64 + k]);
-
-    // AZ and AH arrive with the row-only feature terms folded in; features 2
-    // and 3 (the previous token is the top candidate / among the top four)
-    // and the previous cross logit remain
-    float phi[5];
-    phi[2] = prev_tok == idu[0] ? 1.f : 0.f;
-    phi[3] = (prev_tok == idu[0] || prev_tok == idu[1] || prev_tok == idu[2] || prev_tok == idu[3]) ? 1.f : 0.f;
-
+      for (int k = 0; k < KM; ++k) eh[k] = sv[64 * (S::V0 + k)];
+      int idu[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float gz = az[j] + ptz[j], gh = ah[j] + pth[j];
-      gz += fz[j][2] * phi[2] + fz[j][3] * phi[3] - fz[j][4] * prev_x;
-      gh += fh[j][2] * phi[2] + fh[j][3] * phi[3] - fh[j][4] * prev_x;
-      const float z = sigmoid_rcp(gz);
-      u[j] = (1.f - z) * u[j] + z * gh;
+      for (int k = 0; k < 4; ++k) idu[k] = __float_as_int(sc[64 + k]);
+      // AZ and AH arrive with the row-only feature terms folded in; features 2
+      // and 3 (the previous token is the top candidate / among the top four)
+      // and the previous cross logit remain
+      phi2 = prev_tok == idu[0] ? 1.f : 0.f;
+      phi3 = (prev_tok == idu[0] || prev_tok == idu[1] || prev_tok == idu[2] || prev_tok == idu[3]) ? 1.f : 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float gz = az[j] + ptz[j], gh = ah[j] + pth[j];
+        gz += fz[j][2] * phi2 + fz[j][3] * phi3 - fz[j][4] * prev_x;
+        gh += fh[j][2] * phi2 + fh[j][3] * phi3 - fh[j][4] * prev_x;
+        const float z = sigmoid_rcp(gz);
+        u[j] = (1.f - z) * u[j] + z * gh;
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < KM; ++k) eh[k] = sv[64 * (S::V0 + k)];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) u[j] = ptz[j] * u[j] + pth[j];
     }
 
     float v[KM + 1];
@@ -1595,9 +1697,9 @@ __global__ __launch_bounds__(128) void scan_pc_kernel(ScanArgs a, const int32_t*
     dsum = swap32_sum(dsum);
     float gsum = row_sum16(v[KM]);
     gsum = swap32_sum(swap16_sum(gsum));
-    // the row's part of the pre-activation (b_g and features 0, 1 and the
+    // without GATE the row's part of the pre-activation (b_g and features 0, 1 and the
     // logit half of 4) waits in word 63 of the slot's logit vector
-    const float s = gsum + s_row + wgphi[2] * phi[2] + wgphi[3] * phi[3] - wgphi[4] * prev_x;
+    const float s = !GATE ? gsum + sc[63] + wgphi[2] * phi2 + wgphi[3] * phi3 - wgphi[4] * prev_x : gsum + prev_x;
     const float g = sig_alpha * sigmoid_rcp(s);
 
     // refined logits and their argmax (the first maximum: smallest k on
@@ -1612,8 +1714,8 @@ __global__ __launch_bounds__(128) void scan_pc_kernel(ScanArgs a, const int32_t*
     const int kstar = __builtin_amdgcn_readfirstlane(key);
     const int sel = __builtin_amdgcn_readlane(ci_l, kstar);
     prev_x = readlane_f32(xs_l, kstar);
-    ptz = sv[64 * (2 + KM + kstar)];
-    pth = sv[64 * (2 + 2 * KM + kstar)];
+    ptz = sv[64 * (S::V0 + KM + kstar)];
+    pth = sv[64 * (S::V0 + 2 * KM + kstar)];
     prev_tok = sel;
 
     float ov = g;
@@ -1699,10 +1801,10 @@ Layout rerank_layout(const brisk_corrector& c, int B, int L, int K, bool tab) {
   l.U0 = take(S * l.sU0);
   l.X = take(NP);
   l.SB = take(rows * (2 + 3 * static_cast<size_t>(K)) * step_vec_stride(ds));
-  l.TZA = take(static_cast<size_t>(B) * ds);
-  l.THA = take(static_cast<size_t>(B) * ds);
-  l.FZ = take(5 * ds);
-  l.FH = take(5 * ds);
+  l.TZA = take(static_cast<size_t>(B) * step_vec_stride(ds));
+  l.THA = take(static_cast<size_t>(B) * step_vec_stride(ds));
+  l.FZ = take(5 * step_vec_stride(ds));
+  l.FH = take(5 * step_vec_stride(ds));
   l.DUMP = take(static_cast<size_t>(B) * 64);
   l.total = off;
   return l;
@@ -1738,7 +1840,7 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
   const Layout lay = rerank_layout(c, B, L, K, tab);
   char* base = static_cast<char*>(ws);
   auto F = [&](size_t off) { return reinterpret_cast<float*>(base + off); };
-  const int rows = B * L, NC = rows * K, NP = NC + B;
+  const int rows = B * L, NC = rows * K;
   const int ds = c.d_state;
   const int d_in = c.d_hproj + c.d_tproj + c.d_pos + c.d_feat;
   const int tp_off = c.d_hproj, pos_off = c.d_hproj + c.d_tproj, feat_off = pos_off + c.d_pos;
@@ -1795,18 +1897,25 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
   // 76.3 us with gathering at 64 x 32 rows, and 165 against 140 us at
   // 256 x 16, so the scan gathers from 64 sequences on.
   const bool scan_gathers = tab && pc && K <= 8 && B >= 64;
-  // Without it the scan reads whole step blocks and the table rows are
-  // copied in, kFillBatch rows a wavefront at a time.  Up to 4096 rows
-  // (4 MiB) the projection launch copies them, which saves a launch
-  // (32 rows: 2.5 us of a rerank's 43); more would stretch that launch
-  // (512 x 16 rows: 24 us against 15 + 8 us for two launches).
   const size_t vsz = step_vec_stride(ds);
   float* SB = F(lay.SB);
-  const bool fill = finish && tab && !scan_gathers;
-  const int n_vec = fill ? rows * 3 * K + 2 * B : 0;
-  const bool fill_here = fill && n_vec <= 4096;
-  const FillArgs fargs{c.tables, cand_id, anchor_tok, SB, F(lay.TZA), F(lay.THA), fill ? rows : 0, K,
-                       fill ? B : 0, V, ds, static_cast<int>(vsz)};
+  // Otherwise the table rows reach the step blocks in a pass: copied, or
+  // turned into u = a u + b by gate_kernel, which always feeds the multi-wave
+  // scan (64 x 32 rows, K = 24: 518 -> 291 us).  For the single-wave scan the
+  // gate pass takes about 0.46 us more than a copy per 1000 candidates and
+  // saves 0.42 us a step with more than 8 keys, 0.17 us with up to 8, which
+  // makes a bound on B * K (the whole rerank, gate against copy: 16 x 32 rows,
+  // K = 16 67 : 70 us; 24 x 24, K = 8 44 : 47; 59 x 9, K = 16 48 : 47; 60 x 64,
+  // K = 8 124 : 122; 231 x 13, K = 11 100 : 91; 256 x 16, K = 16 173 : 151).
+  // Without the tables it is a pass more (64 x 16, K = 8: 89 : 79).  Up to
+  // 4096 rows with K <= 8 the projection launch copies on the side, which
+  // costs no pass (1 x 32 rows, a step: 207.9 us with the gate, 206.2).
+  const int n_vec = rows * 3 * K + 2 * B;
+  const bool fill_here = finish && tab && pc && K <= 8 && !scan_gathers && n_vec <= 4096;
+  const bool gate = !pc || (tab && !scan_gathers && !(K <= 8 && n_vec <= 4096) &&
+                            static_cast<int64_t>(B) * K <= (K > 8 ? 900 : 370));
+  const bool fill = finish && tab && !scan_gathers && !gate && !fill_here;
+  const FillArgs fargs{c.tables, cand_id, anchor_tok, SB, F(lay.TZA), F(lay.THA), rows, K, B, V, static_cast<int>(vsz)};
   if (fill_here) pj.fill = fargs;
   const int fill_x =
       fill_here ? std::min(((n_vec + 4 * kFillBatch - 1) / (4 * kFillBatch) + S - 1) / S, (4096 + S - 1) / S) : 0;
@@ -1818,7 +1927,7 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
     else
       hipLaunchKernelGGL(gather_proj_kernel<64>, dim3(gx, gy, S), dim3(256), 0, s, pj);
   }
-  if (fill && !fill_here)
+  if (fill)
     hipLaunchKernelGGL(fill_kernel, dim3((n_vec + 4 * kFillBatch - 1) / (4 * kFillBatch)), dim3(256), 0, s, fargs);
 
   if (S > 1) {
@@ -1859,18 +1968,17 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
   const LiftTerm none{nullptr, 0, 0, 0, 0, 0, nullptr, 0, 0, 0, 0};
   const LiftTerm posz = term(c.pos_emb, 1, c.d_pos, 1, L, c.d_pos, c.W_z + pos_off, d_in, 1);
   const LiftTerm posh = term(c.pos_emb, 1, c.d_pos, 1, L, c.d_pos, c.W_h + pos_off, d_in, 1);
-  const size_t vds = static_cast<size_t>(ds);
   lj.job[0] = LiftJob{{fterm(F(lay.PE), c.d_tproj, c.W_z + tp_off, d_in, 1), none}, fc, SB + (2 + K) * vsz, K, blk, vsz};
   lj.job[1] = LiftJob{{fterm(F(lay.PE), c.d_tproj, c.W_h + tp_off, d_in, 1), none}, fc, SB + (2 + 2 * K) * vsz, K, blk, vsz};
   lj.job[2] = LiftJob{{fterm(F(lay.PC), c.rank, c.W_s, 1, ds), none}, fc, SB + 2 * vsz, K, blk, vsz};
   lj.job[3] = LiftJob{{fterm(F(lay.PH), c.d_hproj, c.W_z, d_in, 1), posz}, hr, SB, 1, blk, vsz};
   lj.job[4] = LiftJob{{fterm(F(lay.PH), c.d_hproj, c.W_h, d_in, 1), posh}, hr, SB + vsz, 1, blk, vsz};
-  lj.job[5] = LiftJob{{fterm(PEa, c.d_tproj, c.W_z + tp_off, d_in, 1), none}, fa, F(lay.TZA), 1, vds, vds};
-  lj.job[6] = LiftJob{{fterm(PEa, c.d_tproj, c.W_h + tp_off, d_in, 1), none}, fa, F(lay.THA), 1, vds, vds};
+  lj.job[5] = LiftJob{{fterm(PEa, c.d_tproj, c.W_z + tp_off, d_in, 1), none}, fa, F(lay.TZA), 1, vsz, vsz};
+  lj.job[6] = LiftJob{{fterm(PEa, c.d_tproj, c.W_h + tp_off, d_in, 1), none}, fa, F(lay.THA), 1, vsz, vsz};
   // feature maps W_z[:, feat] P_phi and W_h[:, feat] P_phi as [5, ds]: input row f is column f of P_phi
-  lj.job[7] = LiftJob{{term(c.P_phi, 1, 1, 5, 0, c.d_feat, c.W_z + feat_off, d_in, 1), none}, hoist ? 5 : 0, F(lay.FZ), 1, vds, vds};
-  lj.job[8] = LiftJob{{term(c.P_phi, 1, 1, 5, 0, c.d_feat, c.W_h + feat_off, d_in, 1), none}, hoist ? 5 : 0, F(lay.FH), 1, vds, vds};
-  const int lift_cols = static_cast<int>(vsz > vds ? vsz : vds);
+  lj.job[7] = LiftJob{{term(c.P_phi, 1, 1, 5, 0, c.d_feat, c.W_z + feat_off, d_in, 1), none}, hoist ? 5 : 0, F(lay.FZ), 1, vsz, vsz};
+  lj.job[8] = LiftJob{{term(c.P_phi, 1, 1, 5, 0, c.d_feat, c.W_h + feat_off, d_in, 1), none}, hoist ? 5 : 0, F(lay.FH), 1, vsz, vsz};
+  const int lift_cols = static_cast<int>(vsz);
   int lift_rows = 0;
   for (int j = 0; j < kMaxLiftJobs; ++j) lift_rows = lj.job[j].n > lift_rows ? lj.job[j].n : lift_rows;
   const dim3 lift_grid((lift_rows + LT_BN - 1) / LT_BN, (lift_cols + LT_BJ - 1) / LT_BJ, kMaxLiftJobs);
@@ -1886,6 +1994,15 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
     else hipLaunchKernelGGL(lift_kernel<2>, lift_grid, dim3(256), 0, s, lj);
   }
   if (!finish) return;
+
+  if (gate) {
+    const GateArgs ga{c.tables, cand_id, anchor_tok, cand_logit, SB, F(lay.TZA), F(lay.THA), F(lay.X), F(lay.FZ),
+                      F(lay.FH), c.w_g, c.b_g, B, L, K, V, ds, static_cast<int>(vsz)};
+    const int64_t waves = static_cast<int64_t>(rows) * ((K + kGateGroup - 1) / kGateGroup) + B;
+    const dim3 grid(static_cast<unsigned>((waves + 3) / 4));
+    if (vsz % 4 == 0) hipLaunchKernelGGL(gate_kernel<4>, grid, dim3(256), 0, s, ga);
+    else hipLaunchKernelGGL(gate_kernel<1>, grid, dim3(256), 0, s, ga);
+  }
 
   ScanArgs sa{};
   sa.B = B; sa.L = L; sa.K = K; sa.ds = ds; sa.vs = static_cast<int>(vsz);
@@ -1905,12 +2022,12 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
     sa.correction = correction;
   }
   const int nw = (ds + 63) / 64;
-  if (scan_gathers)
-    hipLaunchKernelGGL((scan_pc_kernel<8, 4, true>), dim3(B), dim3(128), 0, s, sa, cand_id);
-  else if (ds <= 256 && K <= 8)
-    hipLaunchKernelGGL((scan_pc_kernel<8, 4, false>), dim3(B), dim3(128), 0, s, sa, cand_id);
-  else if (ds <= 256 && K <= 16)
-    hipLaunchKernelGGL((scan_pc_kernel<16, 3, false>), dim3(B), dim3(128), 0, s, sa, cand_id);
+  auto launch_pc = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(B), dim3(128), 0, s, sa, cand_id); };
+  if (scan_gathers) launch_pc(scan_pc_kernel<8, 4, ScanIn::kGather>);
+  else if (pc && K <= 8 && gate) launch_pc(scan_pc_kernel<8, 4, ScanIn::kGate>);
+  else if (pc && K <= 8) launch_pc(scan_pc_kernel<8, 4, ScanIn::kBlocks>);
+  else if (pc && gate) launch_pc(scan_pc_kernel<16, 3, ScanIn::kGate>);
+  else if (pc) launch_pc(scan_pc_kernel<16, 3, ScanIn::kBlocks>);
   else if (K <= 8) launch_scan<8, 4>(sa, B, nw, s);
   else if (K <= 16) launch_scan<16, 3>(sa, B, nw, s);
   else launch_scan<64, 1>(sa, B, nw, s);
