@@ -1073,21 +1073,20 @@ __global__ __launch_bounds__(256) void gate_kernel(GateArgs a) {
     float wphi[5];
 #pragma unroll
     for (int f = 0; f < 5; ++f) wphi[f] = bf16_to_f32(a.w_g[ds + f]);
-    const float row = a.b_g + wphi[0] * p0 + wphi[1] * p1;
 #pragma unroll
     for (int q = 0; q < kGateGroup; ++q) {
       const int t = tok[q];
       phi2[q] = t == i0 ? 1.f : 0.f;
       phi3[q] = t == i0 || t == i1 || t == i2 || t == i3 ? 1.f : 0.f;
       xq[q] = x[min(q, nk - 1)];
-      gate[q] = row + wphi[2] * phi2[q] + wphi[3] * phi3[q] + wphi[4] * (c0 - xq[q]);
+      gate[q] = a.b_g + wphi[0] * p0 + wphi[1] * p1 + wphi[2] * phi2[q] + wphi[3] * phi3[q] + wphi[4] * (c0 - xq[q]);
     }
   }
 #pragma unroll
   for (int q = 0; q < kGateGroup; ++q) tok[q] = clamp_id(tok[q], a.V);
   for (int e = lane * W; e < vs; e += 64 * W) {
     // every load before the first store
-    vec tz[kGateGroup], th[kGateGroup], eh[kGateGroup], az, ah, fz[3], fh[3];
+    vec tz[kGateGroup], th[kGateGroup], eh[kGateGroup], az, ah, fz[5], fh[5];
     float* sb = a.SB + (is_anchor ? 0 : static_cast<size_t>(r) * F * vs) + e;
 #pragma unroll
     for (int q = 0; q < kGateGroup; ++q) {
@@ -1111,12 +1110,10 @@ __global__ __launch_bounds__(256) void gate_kernel(GateArgs a) {
       az = *reinterpret_cast<const vec*>(sn);
       ah = *reinterpret_cast<const vec*>(sn + vs);
       auto feat = [&](const float* m, int f) { return *reinterpret_cast<const vec*>(m + static_cast<size_t>(f) * vs + e); };
-      az += feat(a.FZ, 0) * p0 + feat(a.FZ, 1) * p1;
-      ah += feat(a.FH, 0) * p0 + feat(a.FH, 1) * p1;
 #pragma unroll
-      for (int f = 0; f < 3; ++f) {
-        fz[f] = feat(a.FZ, 2 + f);
-        fh[f] = feat(a.FH, 2 + f);
+      for (int f = 0; f < 5; ++f) {
+        fz[f] = feat(a.FZ, f);
+        fh[f] = feat(a.FH, f);
       }
     }
 #pragma unroll
@@ -1127,10 +1124,14 @@ __global__ __launch_bounds__(256) void gate_kernel(GateArgs a) {
       vec oa, ob;
 #pragma unroll
       for (int j = 0; j < W; ++j) {
-        const float p4 = c0 - xq[q];
-        const float gz = az[j] + tz[q][j] + fz[0][j] * phi2[q] + fz[1][j] * phi3[q] + fz[2][j] * p4;
-        const float gh = ah[j] + th[q][j] + fh[0][j] * phi2[q] + fh[1][j] * phi3[q] + fh[2][j] * p4;
-        const float z = sigmoid_rcp(gz);
+        const float p[5] = {p0, p1, phi2[q], phi3[q], c0 - xq[q]};
+        float gz = az[j] + tz[q][j], gh = ah[j] + th[q][j];
+#pragma unroll
+        for (int f = 0; f < 5; ++f) {
+          gz += fz[f][j] * p[f];
+          gh += fh[f][j] * p[f];
+        }
+        const float z = sigmoidf_(gz);  // with the exact division: this pass waits for memory
         const bool in = e + j < ds;  // the padding of the state stays zero
         oa[j] = in ? 1.f - z : 0.f;
         ob[j] = in ? z * gh : 0.f;
