@@ -735,7 +735,7 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
                 const float v = acc[x][y][q];
-                if constexpr (M == 2) t2 = fmaxf(t2, fminf(t1, v));
+                if constexpr (M == 2) t2 = v > t1 ? t1 : fmaxf(t2, v);  // a NaN leaves both as they are
                 t1 = fmaxf(t1, v);
               }
             const int p = wr * C::WR + y * 16 + l15;
