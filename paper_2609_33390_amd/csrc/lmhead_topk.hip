@@ -693,8 +693,7 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
     if constexpr (kFilt) {
       const bool whole = vend - v0 == C::BV;
       // seed the first two tiles; after them the two lists bound tightly (a
-      // partial second tile too: the first has left a finite bound, so the
-      // rows masked below never pass)
+      // partial second tile too)
       const bool seed = kSeed && (tl == 0 ? whole : tl == 1);
       if (tl > 0 || seed) {
         // lane l holds, for position wr*WR + y*16 + l%16, the logits of
@@ -707,14 +706,18 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
         static_assert((C::QCAP & (C::QCAP - 1)) == 0, "queue slots");
         auto qslot = [](int p, int i) { return p * C::QCAP + (i ^ (p & (C::QCAP - 1))); };
         const int vl0 = v0 + wv * C::WV + 4 * (lane >> 4);
-        if (vend - v0 < C::BV) {  // the share's last tile: rows past its end never enter
+        // The share's last tile: rows past its end become NaN, which no
+        // maximum keeps and no threshold lets pass.  (The lowest finite value
+        // passed wherever a row had left no bound, for its logits are NaN, or
+        // one of -inf.)
+        if (vend - v0 < C::BV) {
 #pragma unroll
           for (int x = 0; x < C::TV; ++x)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
               if (vl0 + x * 16 + q >= vend)
 #pragma unroll
-                for (int y = 0; y < C::TR; ++y) acc[x][y][q] = -3.0e38f;
+                for (int y = 0; y < C::TR; ++y) acc[x][y][q] = __builtin_nanf("");
         }
         if (seed) {
           // Seed from the tile itself: each of the 16 lanes that hold a

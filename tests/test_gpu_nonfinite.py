@@ -34,3 +34,46 @@ def test_nan_tokens_leave_the_finite_ones_their_places(rows, K):
     cl, ci = _propose(H, W, K)
     ol = oracle.lm_logits(oracle.bf16_to_f64(synth.bf16_bits(H)), synth.bf16_bits(W))
     check_candidates(cl.numpy(), ci.numpy(), np.where(np.isnan(ol), -1e30, ol))
+
+
+# the last tile of a share holds 240 or 224 of 256 tokens (126464 in 256 or
+# 128 equal shares), or 240 of the last whole-tile run
+PARTIAL = [(20, 126464, 8), (33, 126464, 8), (64, 126464, 16), (100, 126464, 8), (128, 126464, 16),
+           (200, 256 * 600 - 16, 8), (300, 256 * 600 - 16, 16), (1000, 256 * 600 - 16, 8), (40, 126464, 24)]
+
+
+@pytest.mark.parametrize("rows,V,K", PARTIAL)
+def test_a_nan_row_has_no_candidates(rows, V, K):
+    """No token of a row of NaNs enters its lists, and no place past the end
+    of a share does: every id is -1, and the verifier's token too."""
+    d = 256
+    g = torch.Generator().manual_seed(rows)
+    H = torch.randn(rows, d, generator=g).to(torch.bfloat16)
+    W = (torch.randn(V, d, generator=g) * 0.1).to(torch.bfloat16)
+    ref = _propose(H, W, K)
+    bad = rows // 2
+    H[bad] = float("nan")
+    cl, ci = _propose(H, W, K)
+    assert (ci[bad] == -1).all() and cl[bad].isnan().all()
+    keep = torch.arange(rows) != bad
+    assert torch.equal(cl[keep], ref[0][keep]) and torch.equal(ci[keep], ref[1][keep])
+    _, _, tok = brisk.propose_verify(H.to(DEV), W.to(DEV), 1, K)
+    assert int(tok[bad - 1]) == -1
+
+
+@pytest.mark.parametrize("rows,V,K", PARTIAL)
+def test_minus_infinite_logits_come_before_places_without_a_token(rows, V, K):
+    """Rows with an infinite element: a few tokens have a logit of -inf, all
+    others NaN.  Those few come out in id order, then empty places."""
+    d = 256
+    g = torch.Generator().manual_seed(rows + 1)
+    H = torch.randn(rows, d, generator=g).to(torch.bfloat16)
+    W = (torch.randn(V, d, generator=g) * 0.1).to(torch.bfloat16)
+    H[::7, 0] = float("inf")
+    W[:, 0] = 0
+    few = torch.randperm(V, generator=g)[:K - 3].sort().values
+    W[few, 0] = -1
+    cl, ci = _propose(H, W, K)
+    want = torch.cat([few, torch.full((3,), -1)]).to(torch.int32)
+    assert torch.equal(ci[::7], want.expand(ci[::7].shape))
+    assert (cl[::7, :K - 3] == -float("inf")).all() and cl[::7, K - 3:].isnan().all()
