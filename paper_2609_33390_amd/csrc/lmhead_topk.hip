@@ -578,8 +578,9 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
       // have landed by the end of phase 4g + 3, before slice g + 1 is read.
       stage_sync<0>();
       if (wr == 1) phase_end();
-      // RAGGED: the last slice of a ragged d, whose chunks past d hold other
-      // data; the lm_head operand is zeroed there
+      // RAGGED: the last slice of a ragged d, whose chunks past d hold the
+      // next rows' data; both operands are zeroed there (a zero in one alone
+      // makes NaN of an infinity in the other)
       auto slice = [&]<bool RAGGED>(int g) {
         const unsigned char* sb = smem + (g % C::STAGES) * C::STAGE_BYTES;
         bf16x8 b[C::TR], a[C::TV];
@@ -589,9 +590,12 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
         for (int kk = 0; kk < 2; ++kk) {
           read_frags(sb, kk, a, b);
           if constexpr (RAGGED) {
+            if (kk * 4 + (lane >> 4) >= tail) {
 #pragma unroll
-            for (int x = 0; x < C::TV; ++x)
-              if (kk * 4 + (lane >> 4) >= tail) a[x] = bf16x8{};
+              for (int x = 0; x < C::TV; ++x) a[x] = bf16x8{};
+#pragma unroll
+              for (int y = 0; y < C::TR; ++y) b[y] = bf16x8{};
+            }
           }
           if (kk == 1 && wr == 1) vm_wait();
           lds_wait();
@@ -616,10 +620,11 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
       if (computer) issue(g + C::STAGES - 1);    // refills the buffer slice g-1 used
       const unsigned char* sb = smem + (g % C::STAGES) * C::STAGE_BYTES;
       if (tail && kt == nk - 1) {
-        // chunks past d hold re-read data: zero them in the lm_head tile
+        // chunks past d hold the next rows' data: zero them in both tiles (a
+        // zero in one alone makes NaN of an infinity in the other)
         unsigned char* wb = smem + (g % C::STAGES) * C::STAGE_BYTES;
         const int nz = C::CPR - tail;
-        for (int idx = tid; idx < C::BV * nz; idx += C::NTA) {
+        for (int idx = tid; idx < C::ROWS * nz; idx += C::NTA) {
           const int R = idx / nz, c = tail + idx % nz;
           *reinterpret_cast<uint4*>(wb + (R * C::CPR + swz<C::CPR>(R, c)) * 16) = make_uint4(0, 0, 0, 0);
         }

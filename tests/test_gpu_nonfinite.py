@@ -77,3 +77,41 @@ def test_minus_infinite_logits_come_before_places_without_a_token(rows, V, K):
     want = torch.cat([few, torch.full((3,), -1)]).to(torch.int32)
     assert torch.equal(ci[::7], want.expand(ci[::7].shape))
     assert (cl[::7, :K - 3] == -float("inf")).all() and cl[::7, K - 3:].isnan().all()
+
+
+@pytest.mark.parametrize("d", [72, 200, 1000])
+@pytest.mark.parametrize("rows,K", [(20, 8), (20, 64), (60, 16), (60, 24), (100, 8), (200, 8), (300, 16), (300, 24)])
+def test_an_infinite_row_leaves_its_neighbours_alone(rows, K, d):
+    """A ragged d: the last slice of a row's copy runs into the next row, whose
+    infinities and NaNs must not reach the products."""
+    V = 256 * 300 + 9
+    g = torch.Generator().manual_seed(rows + d)
+    H = torch.randn(rows, d, generator=g).to(torch.bfloat16).to(DEV)
+    W = (torch.randn(V, d, generator=g) * 0.1).to(torch.bfloat16).to(DEV)
+    ref = brisk.propose_block(H, W, K)
+    bad = torch.zeros(rows, dtype=torch.bool, device=DEV)
+    bad[1::5] = True
+    H[1::10, :] = float("inf")
+    H[6::10, :] = float("nan")
+    out = brisk.propose_block(H, W, K)
+    for a, b in zip(out, ref):
+        assert torch.equal(a[~bad], b[~bad])
+
+
+@pytest.mark.parametrize("rows", [20, 60, 300])
+def test_an_infinite_verifier_row_leaves_its_neighbours_alone(rows):
+    d, V, K = 72, 256 * 300 + 9, 8
+    g = torch.Generator().manual_seed(rows)
+    H = torch.randn(rows, d, generator=g).to(torch.bfloat16).to(DEV)
+    W = (torch.randn(V, d, generator=g) * 0.1).to(torch.bfloat16).to(DEV)
+    ids = torch.rand(rows, 1000, generator=g).argsort(1)[:, :K].to(torch.int32).to(DEV)
+    prob = torch.full((rows, K), 1.0 / K, device=DEV)
+    u = torch.rand(rows, generator=g).to(DEV)
+    run = lambda: brisk.spec_verify(H, W, ids[:, :1].contiguous(), ids, prob, u, 5)  # noqa: E731
+    ref = run()
+    H[1::5] = float("inf")
+    out = run()
+    keep = torch.ones(rows, dtype=torch.bool, device=DEV)
+    keep[1::5] = False
+    for k in ("row_accept", "row_resample"):
+        assert torch.equal(out[k].view(-1)[keep], ref[k].view(-1)[keep])
