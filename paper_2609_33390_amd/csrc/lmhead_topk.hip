@@ -1178,6 +1178,14 @@ Plan make_plan(int rows, int V, int K, bool sample = false) {
   // the sampling pass and lists longer than kFiltKeys fold staged logits
   if (sample || K > kFiltKeys) return rows <= 64 ? make_plan_for<MidRows>(1, rows, V, K) : make_plan_for<Rows256>(4, rows, V, K);
   if (rows <= 64) return make_plan_for<Rows64>(1, rows, V, K);
+  // Beyond one row tile of 128 per compute unit every share is the whole
+  // vocabulary, and what counts is how many rounds the row tiles take.  The
+  // 256-row tile takes the fewest, 128- / 192- / 256-row tile at 32000 x 512:
+  // 32769 rows 2250 / 1663 / 1858 us, 49153 rows 2360 / 3210 / 1937, 65536
+  // rows 2398 / 3337 / 2083, 131072 rows 4778 / 5019 / 4044; at 50000 x 2048:
+  // 12.1 / 9.2 / 8.8 ms, 12.3 / 18.6 / 10.1, 13.0 / 18.3 / 11.4, 25.0 / 28.4 /
+  // 22.0.
+  if (rows > Rows128::BR * kTargetWorkgroups) return make_plan_for<Rows256>(4, rows, V, K);
   // Above 64 rows, the tile with the least padding by plan_cost.  Measured at
   // 126464 x 4096, 128- / 192- / 256-row tile in us: 192 rows 298 / 258 / 270,
   // 256 rows 315 / 394 / 286, 320 rows 425 / 416 / 437, 512 rows 564 / 599 /
@@ -1482,6 +1490,13 @@ void launch_spec_verify(const uint16_t* Hv, const uint16_t* W, int B, int L, int
   int32_t* rr = row_resample ? row_resample : reinterpret_cast<int32_t*>(base + l.rows_res);
   launch_spec_kp<4>(l.plan, Hv, W, B, L, d, V, K, proposal, cand_id, cand_prob, u_accept, sa, partial, ra, rr,
                     accept_len, correction, s);
+}
+
+void propose_plan_info(int rows, int V, int K, int* out) {
+  const Plan p = make_plan(rows, V, K);
+  constexpr int kRows[] = {SmallRows::BR, Rows64::BR, Rows128::BR, Rows192::BR, Rows256::BR};
+  out[0] = kRows[p.cfg];
+  out[1] = p.n_rtiles * p.n_groups;
 }
 
 size_t propose_workspace_bytes(int rows, int V, int K) {
