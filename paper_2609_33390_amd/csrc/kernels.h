@@ -12,8 +12,9 @@ namespace brisk {
 // ---- propose: LM head + fused top-K + merge --------------------------------
 size_t propose_workspace_bytes(int rows, int V, int K);
 // What the pass of these sizes runs on, for checks on the host: out[0] = rows of
-// a row tile, out[1] = workgroups.
-void propose_plan_info(int rows, int V, int K, int* out);
+// a row tile, out[1] = workgroups, out[2] = whether lm_head copies are
+// non-temporal (for a line-aligned matrix).
+void propose_plan_info(int rows, int d, int V, int K, int* out);
 // rows = proposal rows (K candidates each) followed by verifier rows (argmax
 // each): rows_prop of them are proposal rows.
 // The two launches of launch_propose: the LM-head pass (per-group ordered

@@ -275,7 +275,7 @@ __device__ __forceinline__ bool is_candidate_reg(const int (&ids)[N], uint64_t m
 // that all workgroups re-read: 32 rows 175 -> 168 us, 64 rows 198 -> 187, 96
 // rows 190 -> 182, 256 rows 281 -> 272 (126464 x 4096).  Rows that several
 // workgroups read are better kept (512 rows 476 -> 477, 4096 rows 3234 ->
-// 3470 us).
+// 3470 us), and so is an lm_head that fits the last-level cache (streams()).
 template <class C, int KP, bool SAMPLE = false, bool STREAM = false>
 __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA / 256, C::NTA / 256))) void lmhead_topk_kernel(
     const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, int rows, int d, int V,
@@ -1196,6 +1196,23 @@ Plan make_plan(int rows, int V, int K, bool sample = false) {
   return c4 <= c2 && c4 <= c3 ? p4 : (c3 <= c2 ? p3 : p2);
 }
 
+// Whether the lm_head copies are non-temporal (STREAM, see the kernel): with
+// one row tile, unless
+//  - its rows are not whole 128-byte lines: neighbouring slices then share
+//    lines, which must stay in L2 (248 rows x 131072 tokens, d = 1896: 196 us
+//    non-temporal, 176 not);
+//  - the matrix fits the 256 MiB last-level cache, where the next call finds it
+//    if it was read as usual.  Not / non-temporal at 4, 32, 128 and 256 rows in
+//    us: 195 MiB (50000 x 2048) 46.5 / 48.6, 47.7 / 51.3, 51.2 / 61.9, 67.3 /
+//    77.4; 250 MiB (32000 x 4096) 59.9 / 62.2, 61.6 / 65.0, 73.5 / 84.7, 80.4 /
+//    86.8; 292 MiB (75000 x 2048) 67.5 / 65.8, 69.4 / 67.4, 98.4 / 103.4, 121.0
+//    / 124.4; 390 MiB (50000 x 4096) 82.7 / 79.2, 84.6 / 80.8, 93.7 / 90.0,
+//    131.7 / 129.3.
+bool streams(const Plan& p, const uint16_t* W, int d, int V) {
+  const bool lines = d % 64 == 0 && (reinterpret_cast<uintptr_t>(W) & 127u) == 0;
+  return p.n_rtiles == 1 && lines && static_cast<size_t>(V) * d * 2 > (size_t{256} << 20);
+}
+
 template <class C, int KP, bool SAMPLE, bool STREAM>
 void launch_tile_as(const Plan& p, const uint16_t* H, const uint16_t* W, int rows, int d, int V,
                     uint64_t* partial, hipStream_t s, const SampleArgs& sa) {
@@ -1207,11 +1224,7 @@ void launch_tile_as(const Plan& p, const uint16_t* H, const uint16_t* W, int row
 template <class C, int KP, bool SAMPLE = false>
 void launch_tile(const Plan& p, const uint16_t* H, const uint16_t* W, int rows, int d, int V,
                  uint64_t* partial, hipStream_t s, SampleArgs sa = SampleArgs{}) {
-  // lm_head rows that are not whole 128-byte lines share lines between
-  // neighbouring slices, which must stay in L2 (248 rows x 131072 tokens, d =
-  // 1896: 196 us non-temporal, 176 not)
-  const bool lines = d % 64 == 0 && (reinterpret_cast<uintptr_t>(W) & 127u) == 0;
-  if (p.n_rtiles == 1 && lines) launch_tile_as<C, KP, SAMPLE, true>(p, H, W, rows, d, V, partial, s, sa);
+  if (streams(p, W, d, V)) launch_tile_as<C, KP, SAMPLE, true>(p, H, W, rows, d, V, partial, s, sa);
   else launch_tile_as<C, KP, SAMPLE, false>(p, H, W, rows, d, V, partial, s, sa);
 }
 
@@ -1492,11 +1505,12 @@ void launch_spec_verify(const uint16_t* Hv, const uint16_t* W, int B, int L, int
                     accept_len, correction, s);
 }
 
-void propose_plan_info(int rows, int V, int K, int* out) {
+void propose_plan_info(int rows, int d, int V, int K, int* out) {
   const Plan p = make_plan(rows, V, K);
   constexpr int kRows[] = {SmallRows::BR, Rows64::BR, Rows128::BR, Rows192::BR, Rows256::BR};
   out[0] = kRows[p.cfg];
   out[1] = p.n_rtiles * p.n_groups;
+  out[2] = streams(p, nullptr, d, V);
 }
 
 size_t propose_workspace_bytes(int rows, int V, int K) {

@@ -8,10 +8,11 @@ import paper_2609_33390_amd as brisk
 CUS = 256
 
 
-def _plan(rows, V, K):
-    fn = getattr(brisk.lib(), "_ZN5brisk17propose_plan_infoEiiiPi")   # internal, not part of the C ABI
-    out = (ctypes.c_int * 2)()
-    fn(rows, V, K, out)
+def _plan(rows, d, V, K):
+    """Rows of a row tile, workgroups, non-temporal lm_head copies."""
+    fn = getattr(brisk.lib(), "_ZN5brisk17propose_plan_infoEiiiiPi")   # internal, not part of the C ABI
+    out = (ctypes.c_int * 3)()
+    fn(rows, d, V, K, out)
     return list(out)
 
 
@@ -20,6 +21,16 @@ def _plan(rows, V, K):
 def test_many_rows_take_the_fewest_rounds(rows, V):
     """Where a row tile's share is the whole vocabulary, the tile with the
     fewest rounds of workgroups."""
-    tile, wgs = _plan(rows, V, 8)
+    tile, wgs, _ = _plan(rows, 8, V, 8)
     assert wgs == -(-rows // tile)
     assert -(-wgs // CUS) == -(-rows // (256 * CUS))
+
+
+@pytest.mark.parametrize("rows,d,V,want", [
+    (4, 768, 20000, 0), (32, 2048, 50000, 0), (64, 1024, 126464, 0), (256, 4096, 32000, 0), (32, 4096, 32768, 0),
+    (32, 4096, 32769, 1), (256, 4096, 50000, 1), (1, 4096, 126464, 1), (64, 3584, 152064, 1),
+    (512, 4096, 126464, 0), (32, 4104, 126464, 0),
+])
+def test_only_an_lm_head_beyond_the_last_level_cache_is_streamed(rows, d, V, want):
+    """Non-temporal copies: one row tile, rows of whole lines, over 256 MiB."""
+    assert _plan(rows, d, V, 8)[2] == want
