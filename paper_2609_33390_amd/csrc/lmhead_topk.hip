@@ -316,6 +316,16 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
     vb = group * tiles_per_group * C::BV;
     ve = min(V, vb + tiles_per_group * C::BV);
   }
+  // A share shorter than a tile (the last one, at 256-row tiles and V just past
+  // a whole number of them) would have to fold every logit: it has no whole
+  // tile to seed a threshold from.  Its tile starts early instead, at the rows
+  // of the share before, which bound the row's KP-th logit as well as its own
+  // and are dropped when the lists take them.  33000 tokens x 1024, 250 rows, 16
+  // keys: 119 -> 63 us.  (V below one tile stays as it is.)
+  const int vlo = vb;
+  if constexpr (kFilt) {
+    if (ve - vb < C::BV) vb = max(0, ve - C::BV);
+  }
   // Tiles of the share: runs of BV rows, the last one partial.  (A short
   // extra tile at the end, to shorten the top-K that cannot overlap with
   // copies, costs more: a slice takes time whether or not its rows exist.)
@@ -450,7 +460,7 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
       for (int q = 0; q < 4; ++q) {
         const int vid = vid0 + q;
         const uint64_t key = make_key(v[q], static_cast<uint32_t>(vid));
-        if (vid < vend && v[q] >= thr && key > list[KP - 1]) {
+        if (vid >= vlo && vid < vend && v[q] >= thr && key > list[KP - 1]) {
           // sampling keeps candidates out: their draws use exact weights
           if constexpr (SAMPLE) {
             if (!row_ok) continue;
@@ -837,7 +847,7 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
           for (int i = consumer ? esub : n; i < n; i += C::TPP) {
             const uint2 e = reinterpret_cast<const uint2*>(sq)[qslot(ep, i)];
             const uint64_t key = make_key(__uint_as_float(e.x), e.y);
-            if (key > list[KP - 1]) list_insert(list, key);
+            if (key > list[KP - 1] && static_cast<int>(e.y) >= vlo) list_insert(list, key);
           }
           publish_floors();
           continue;  // the next slice's barrier ends every read of the queues
@@ -1155,10 +1165,14 @@ Plan make_plan_for(int cfg, int rows, int V, int K, int target = kTargetWorkgrou
   // spare, but no memory traffic).  On the larger tiles a partial tile takes
   // the time of a whole one, and more workgroups only contend for the L2
   // (248 rows x 152064 tokens, d = 1920: 3 tiles each on 198 workgroups 196
-  // us, on 256 with shares 208 us).
+  // us, on 256 with shares 208 us).  The 8-wave tiles seed their thresholds
+  // from a whole first tile, so a share has to hold one: 50000 tokens x 2048 in
+  // 256 shares of 195 against 196 whole tiles, 40 rows 65 : 45 us, 64 rows and
+  // 16 keys 92 : 63 us.
   const int want_all = target / p.n_rtiles < 1 ? 1 : target / p.n_rtiles;
   p.even = 0;
-  if (!C::PINGPONG && !(C::WAVES_R == 2 && p.n_rtiles > 1) && p.n_groups < want_all && V / want_all >= C::BV / 2) {
+  const int least = C::WAVES_R == 2 ? C::BV + 16 : C::BV / 2;  // shares are cut at multiples of 16
+  if (!C::PINGPONG && !(C::WAVES_R == 2 && p.n_rtiles > 1) && p.n_groups < want_all && V / want_all >= least) {
     p.even = 1;
     p.n_groups = want_all;
     p.tiles_per_group = (V / want_all + 16 + C::BV - 1) / C::BV;

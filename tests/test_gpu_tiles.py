@@ -57,3 +57,19 @@ def test_partial_tiles_keep_exact_ties_in_id_order():
     assert int(top.sum()) > 10
     assert torch.equal(ci[top], ids.to(torch.int32).expand(int(top.sum()), K))
     assert torch.equal(cl[top], cl[top][:, :1].expand(-1, K))
+
+
+@pytest.mark.parametrize("left", [1, 17, 100, 255])
+@pytest.mark.parametrize("rows,K", [(40, 8), (64, 16), (100, 4), (128, 16), (200, 8), (250, 16), (520, 8)])
+def test_a_last_share_shorter_than_a_tile(rows, K, left):
+    """The last share has `left` tokens, and its tile starts among the share
+    before: the best tokens lie on both sides of the border, each comes once."""
+    d, V = 128, 156 * 256 + left
+    g = torch.Generator().manual_seed(rows + left)
+    H = torch.randn(rows, d, generator=g).to(torch.bfloat16)
+    W = torch.randn(V, d, generator=g) * 0.05
+    W[-300:] *= 4
+    W = W.to(torch.bfloat16)
+    cl, ci = brisk.propose_block(H.to(DEV), W.to(DEV), K)
+    ol = oracle.lm_logits(oracle.bf16_to_f64(synth.bf16_bits(H)), synth.bf16_bits(W))
+    check_candidates(cl.cpu().numpy(), ci.cpu().numpy(), ol)

@@ -34,3 +34,13 @@ def test_many_rows_take_the_fewest_rounds(rows, V):
 def test_only_an_lm_head_beyond_the_last_level_cache_is_streamed(rows, d, V, want):
     """Non-temporal copies: one row tile, rows of whole lines, over 256 MiB."""
     assert _plan(rows, d, V, 8)[2] == want
+
+
+@pytest.mark.parametrize("rows", [33, 64, 65, 128])
+def test_shares_hold_a_whole_tile(rows):
+    """At 33 to 128 rows thresholds are seeded from a whole 256-token tile:
+    below 256 shares of one tile (cut at multiples of 16) every share but the
+    last is a run of whole tiles."""
+    for V in (20000, 32768, 33000, 50000, 65536, 69631):
+        assert _plan(rows, 2048, V, 8)[1] <= -(-V // 256), V
+    assert _plan(rows, 2048, 69632, 8)[1] == CUS
