@@ -94,7 +94,8 @@ __device__ __forceinline__ FillVec fill_vec(const FillArgs& a, int n, int v) {
 // A wavefront copies kFillBatch consecutive vectors of 256 floats at a time:
 // lane g loads vector g's token id (one load for the batch), then every lane
 // loads its 16 bytes of each source row before the first store, so the batch
-// waits for two memory latencies instead of two per vector.
+// waits for two memory latencies instead of two per vector.  Longer vectors
+// (d_state > 256) are copied one by one.
 constexpr int kFillBatch = 4;
 __device__ void fill_rows(const FillArgs& a, int first, int step) {
   const int lane = threadIdx.x & 63;
@@ -102,6 +103,18 @@ __device__ void fill_rows(const FillArgs& a, int first, int step) {
   // the batch index is wave-uniform
   for (int n0 = __builtin_amdgcn_readfirstlane(first * kFillBatch); n0 < n_all; n0 += step * kFillBatch) {
     const int my_id = fill_id(a, min(n0 + min(lane, kFillBatch - 1), n_all - 1));
+    if (a.vs != 256) {
+      for (int g = 0; g < kFillBatch && n0 + g < n_all; ++g) {
+        const FillVec f = fill_vec(a, n0 + g, __builtin_amdgcn_readlane(my_id, g));
+        if ((a.vs & 3) == 0) {
+          for (int e = lane * 4; e < a.vs; e += 256)
+            *reinterpret_cast<float4*>(f.dst + e) = *reinterpret_cast<const float4*>(f.src + e);
+        } else {
+          for (int e = lane; e < a.vs; e += 64) f.dst[e] = f.src[e];
+        }
+      }
+      continue;
+    }
     // named, not arrays, so that nothing is staged through memory; a batch
     // past the last vector repeats it (the same bytes to the same place)
     static_assert(kFillBatch == 4, "the batch below is written out for four vectors");
@@ -1200,10 +1213,15 @@ struct ScanArgs {
   int V;
 };
 
+// What the multi-wave scan reads of a row.  With GATE the step blocks went
+// through gate_kernel: candidate k feeds u = ta[k] u + tb[k] into the next row,
+// and xs is its gate term.  Otherwise ta and tb are its TZ and TH vectors, xs
+// its cross logit, and the row's own AZ and AH come with them.
 template <int KM>
 struct StepData {
+  float az, ah;  // unused with GATE
   float eh[KM];
-  float ga[KM], gb[KM];  // what candidate k feeds into the next row: u = ga u + gb
+  float ta[KM], tb[KM];
   float cl, xs;
   int ci;
 };
@@ -1216,7 +1234,7 @@ __device__ __forceinline__ float buf_ld(__amdgpu_buffer_rsrc_t r, int voff, int 
 // duplicate of candidate K-1 and lanes past ds read element ds-1; consumers
 // ignore those values (k >= K is never selected or used, lanes past ds hold
 // u = 0, lanes >= K are masked where scores are formed).
-template <int KM>
+template <int KM, bool GATE>
 __device__ __forceinline__ void load_step(StepData<KM>& s, const ScanArgs& a,
                                           __amdgpu_buffer_rsrc_t rsb, int voff, int b, int i,
                                           int lane) {
@@ -1224,12 +1242,16 @@ __device__ __forceinline__ void load_step(StepData<KM>& s, const ScanArgs& a,
   const int F = 2 + 3 * a.K;
   const int vb = a.vs * 4;                // bytes per vector
   const int base = ii * F * vb;           // this row's step block inside the sequence
+  if constexpr (!GATE) {
+    s.az = buf_ld(rsb, voff, base);
+    s.ah = buf_ld(rsb, voff, base + vb);
+  }
 #pragma unroll
   for (int k = 0; k < KM; ++k) {
     const int kk = k < a.K ? k : a.K - 1;
     s.eh[k] = buf_ld(rsb, voff, base + (2 + kk) * vb);
-    s.ga[k] = buf_ld(rsb, voff, base + (2 + a.K + kk) * vb);
-    s.gb[k] = buf_ld(rsb, voff, base + (2 + 2 * a.K + kk) * vb);
+    s.ta[k] = buf_ld(rsb, voff, base + (2 + a.K + kk) * vb);
+    s.tb[k] = buf_ld(rsb, voff, base + (2 + 2 * a.K + kk) * vb);
   }
   const size_t nl = (static_cast<size_t>(b) * a.L + ii) * a.K + (lane < a.K ? lane : a.K - 1);
   s.cl = a.cand_logit[nl];
@@ -1240,7 +1262,7 @@ __device__ __forceinline__ void load_step(StepData<KM>& s, const ScanArgs& a,
 constexpr int kScanOutChunk = 32;  // steps whose outputs are staged in LDS at once
 constexpr int kScanMaxWaves = 8;
 
-template <int KM, int D>
+template <int KM, int D, bool GATE>
 __global__ __launch_bounds__(512) void scan_kernel(ScanArgs a) {
   constexpr int NV = KM + 1;                 // K residual sums + the gate sum
   constexpr int NQ = kScanMaxWaves * 4;      // row sums per value
@@ -1269,10 +1291,19 @@ __global__ __launch_bounds__(512) void scan_kernel(ScanArgs a) {
   const float wgu = ok ? wg_e : 0.f;
   const float sig_alpha = sigmoidf_(a.alpha);
 
-  // what the token before row i feeds into it (gate_kernel)
+  float fz[5] = {}, fh[5] = {}, wgphi[5] = {};
+#pragma unroll
+  for (int f = 0; !GATE && f < 5; ++f) {
+    fz[f] = a.FZ[f * a.vs + ec];
+    fh[f] = a.FH[f * a.vs + ec];
+    wgphi[f] = bf16_to_f32(a.w_g[ds + f]);
+  }
+
+  // what the token before row i feeds into it (see StepData)
   float prev_a = a.TZA[static_cast<size_t>(b) * a.vs + ec];
   float prev_b = a.THA[static_cast<size_t>(b) * a.vs + ec];
-  float prev_g = a.X[NC + b];
+  float prev_x = a.X[NC + b];
+  int prev_tok = a.anchor[b];
   const int my_v = lane < K ? lane : 0;  // the residual sum this lane assembles
 
   auto flush = [&](int i0, int n) {
@@ -1294,7 +1325,27 @@ __global__ __launch_bounds__(512) void scan_kernel(ScanArgs a) {
   };
 
   auto step = [&](const StepData<KM>& c, int i) {
-    u = ok ? prev_a * u + prev_b : 0.f;
+    float phi[5] = {};
+    if constexpr (GATE) {
+      u = ok ? prev_a * u + prev_b : 0.f;
+    } else {
+      const float c0 = readlane_f32(c.cl, 0), c1 = readlane_f32(c.cl, 1), c3 = readlane_f32(c.cl, 3);
+      const int id0 = __builtin_amdgcn_readlane(c.ci, 0);
+      const bool in4 = __ballot(lane < 4 && c.ci == prev_tok) != 0;
+      phi[0] = c0 - c1;
+      phi[1] = c0 - c3;
+      phi[2] = prev_tok == id0 ? 1.f : 0.f;
+      phi[3] = in4 ? 1.f : 0.f;
+      phi[4] = c0 - prev_x;
+      float gz = c.az + prev_a, gh = c.ah + prev_b;
+#pragma unroll
+      for (int f = 0; f < 5; ++f) {
+        gz += fz[f] * phi[f];
+        gh += fh[f] * phi[f];
+      }
+      const float z = sigmoidf_(gz);
+      u = ok ? (1.f - z) * u + z * gh : 0.f;
+    }
 
     float v[NV];
 #pragma unroll
@@ -1322,7 +1373,13 @@ __global__ __launch_bounds__(512) void scan_kernel(ScanArgs a) {
       my_d += (rd.x + rd.y) + (rd.z + rd.w);
       s += (rg.x + rg.y) + (rg.z + rg.w);
     }
-    s += prev_g;
+    if constexpr (GATE) {
+      s += prev_x;
+    } else {
+      s += a.b_g;
+#pragma unroll
+      for (int f = 0; f < 5; ++f) s += wgphi[f] * phi[f];
+    }
     const float g = sig_alpha * sigmoidf_(s);
     my_d = lane < K ? my_d : 0.f;
     const float lt = c.cl + g * my_d;
@@ -1341,26 +1398,27 @@ __global__ __launch_bounds__(512) void scan_kernel(ScanArgs a) {
         o_gam[t] = g;
       }
     }
-    float na = c.ga[0], nb = c.gb[0];
+    float na = c.ta[0], nb = c.tb[0];
 #pragma unroll
     for (int k = 1; k < KM; ++k) {
-      na = k == kstar ? c.ga[k] : na;
-      nb = k == kstar ? c.gb[k] : nb;
+      na = k == kstar ? c.ta[k] : na;
+      nb = k == kstar ? c.tb[k] : nb;
     }
     prev_a = na;
     prev_b = nb;
-    prev_g = readlane_f32(c.xs, kstar);
+    prev_x = readlane_f32(c.xs, kstar);
+    prev_tok = sel;
     if (t == kScanOutChunk - 1 || i == L - 1) flush(i - t, t + 1);
   };
 
   StepData<KM> q[D];
 #pragma unroll
-  for (int t = 0; t < D; ++t) load_step<KM>(q[t], a, rsb, voff, b, t, lane);
+  for (int t = 0; t < D; ++t) load_step<KM, GATE>(q[t], a, rsb, voff, b, t, lane);
   for (int i = 0; i < L; i += D) {
 #pragma unroll
     for (int t = 0; t < D; ++t) {
       if (i + t < L) step(q[t], i + t);
-      load_step<KM>(q[t], a, rsb, voff, b, i + t + D, lane);
+      load_step<KM, GATE>(q[t], a, rsb, voff, b, i + t + D, lane);
     }
   }
 }
@@ -1812,8 +1870,9 @@ Layout rerank_layout(const brisk_corrector& c, int B, int L, int K, bool tab) {
 }
 
 template <int KM, int D>
-void launch_scan(const ScanArgs& sa, int B, int nw, hipStream_t s) {
-  hipLaunchKernelGGL((scan_kernel<KM, D>), dim3(B), dim3(64 * nw), 0, s, sa);
+void launch_scan(const ScanArgs& sa, bool gate, int B, int nw, hipStream_t s) {
+  if (gate) hipLaunchKernelGGL((scan_kernel<KM, D, true>), dim3(B), dim3(64 * nw), 0, s, sa);
+  else hipLaunchKernelGGL((scan_kernel<KM, D, false>), dim3(B), dim3(64 * nw), 0, s, sa);
 }
 
 }  // namespace
@@ -1901,20 +1960,35 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
   const size_t vsz = step_vec_stride(ds);
   float* SB = F(lay.SB);
   // Otherwise the table rows reach the step blocks in a pass: copied, or
-  // turned into u = a u + b by gate_kernel, which always feeds the multi-wave
-  // scan (64 x 32 rows, K = 24: 518 -> 291 us).  For the single-wave scan the
-  // gate pass takes about 0.46 us more than a copy per 1000 candidates and
-  // saves 0.42 us a step with more than 8 keys, 0.17 us with up to 8, which
-  // makes a bound on B * K (the whole rerank, gate against copy: 16 x 32 rows,
-  // K = 16 67 : 70 us; 24 x 24, K = 8 44 : 47; 59 x 9, K = 16 48 : 47; 60 x 64,
-  // K = 8 124 : 122; 231 x 13, K = 11 100 : 91; 256 x 16, K = 16 173 : 151).
-  // Without the tables it is a pass more (64 x 16, K = 8: 89 : 79).  Up to
-  // 4096 rows with K <= 8 the projection launch copies on the side, which
-  // costs no pass (1 x 32 rows, a step: 207.9 us with the gate, 206.2).
+  // turned into u = a u + b by gate_kernel.  Up to 4096 of them the projection
+  // launch copies on the side, which costs no pass (1 x 32 rows, K = 8, a step:
+  // 207.9 us with the gate, 206.2).  Without the tables the gate is a pass more.
+  // The whole rerank, gate : copy (or, without the tables, no pass) in us:
+  //  - single-wave scan.  The gate pass takes about 0.46 us more than a copy per
+  //    1000 candidates and saves 0.42 us a step with more than 8 keys, 0.17 us
+  //    with up to 8, which makes a bound on B * K (16 x 32, K = 16 67 : 70; 24 x
+  //    24, K = 8 44 : 47; 59 x 9, K = 16 48 : 47; 60 x 64, K = 8 124 : 122; 231 x 13,
+  //    K = 11 100 : 91; 256 x 16, K = 16 173 : 151).  Without the tables 64 x 16, K =
+  //    8 89 : 79.
+  //  - multi-wave scan, up to 16 keys (a few vectors a candidate to load, like
+  //    the single-wave one): 8 x 32, K = 8, d_state 320 90 : 96; 64 x 16, K = 4,
+  //    320 72 : 73; 64 x 16, K = 8, 320 80 : 77; 16 x 16, K = 16, 512 90 : 90; 256
+  //    x 4, K = 16, 320 85 : 76; copied on the side 1 x 4, K = 8, 320 45 : 43.
+  //    Without the tables 8 x 32, K = 8, 320 100 : 100; 64 x 16, K = 16, 512 233 :
+  //    206.
+  //  - multi-wave scan, more keys: one row in flight, whose loads, gate and
+  //    state update the pass shortens: 8 x 32, K = 24 270 : 490 with the tables,
+  //    288 : 496 without; 256 x 16, K = 64 661 : 744 and 1319 : 1245; 256 x 4, K =
+  //    32, 512 187 : 242 and 416 : 420; 256 x 16, K = 64, 512 1129 : 1165 and 3200
+  //    : 2895.
   const int n_vec = rows * 3 * K + 2 * B;
-  const bool fill_here = finish && tab && pc && K <= 8 && !scan_gathers && n_vec <= 4096;
-  const bool gate = !pc || (tab && !scan_gathers && !(K <= 8 && n_vec <= 4096) &&
-                            static_cast<int64_t>(B) * K <= (K > 8 ? 900 : 370));
+  const int64_t bk = static_cast<int64_t>(B) * K;
+  const bool beside = n_vec <= 4096;
+  bool gate;
+  if (pc) gate = tab && !scan_gathers && (K > 8 ? bk <= 900 : bk <= 370 && !beside);
+  else if (K <= 16) gate = tab && !beside && bk * static_cast<int64_t>(vsz) <= 80 << 10;
+  else gate = tab || bk * static_cast<int64_t>(vsz) < 4 << 20;
+  const bool fill_here = finish && tab && !scan_gathers && !gate && beside;
   const bool fill = finish && tab && !scan_gathers && !gate && !fill_here;
   const FillArgs fargs{c.tables, cand_id, anchor_tok, SB, F(lay.TZA), F(lay.THA), rows, K, B, V, static_cast<int>(vsz)};
   if (fill_here) pj.fill = fargs;
@@ -2029,9 +2103,9 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
   else if (pc && K <= 8) launch_pc(scan_pc_kernel<8, 4, ScanIn::kBlocks>);
   else if (pc && gate) launch_pc(scan_pc_kernel<16, 3, ScanIn::kGate>);
   else if (pc) launch_pc(scan_pc_kernel<16, 3, ScanIn::kBlocks>);
-  else if (K <= 8) launch_scan<8, 4>(sa, B, nw, s);
-  else if (K <= 16) launch_scan<16, 3>(sa, B, nw, s);
-  else launch_scan<64, 1>(sa, B, nw, s);
+  else if (K <= 8) launch_scan<8, 4>(sa, gate, B, nw, s);
+  else if (K <= 16) launch_scan<16, 3>(sa, gate, B, nw, s);
+  else launch_scan<64, 1>(sa, gate, B, nw, s);
   if (verifier && !pc) launch_verify(selected, verifier, B, L, accept_len, correction, s);
 }
 
