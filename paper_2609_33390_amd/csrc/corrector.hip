@@ -1966,10 +1966,13 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
   // The whole rerank, gate : copy (or, without the tables, no pass) in us:
   //  - single-wave scan.  The gate pass takes about 0.46 us more than a copy per
   //    1000 candidates and saves 0.42 us a step with more than 8 keys, 0.17 us
-  //    with up to 8, which makes a bound on B * K (16 x 32, K = 16 67 : 70; 24 x
-  //    24, K = 8 44 : 47; 59 x 9, K = 16 48 : 47; 60 x 64, K = 8 124 : 122; 231 x 13,
-  //    K = 11 100 : 91; 256 x 16, K = 16 173 : 151).  Without the tables 64 x 16, K =
-  //    8 89 : 79.
+  //    with up to 8, which makes a bound on B * K.  Up to 8 keys: 24 x 24, K = 8
+  //    44 : 47; 46 x 16, K = 8 43 : 45; 60 x 64, K = 8 124 : 122.  More: 16 x 32,
+  //    K = 16 62.4 : 65.5; 64 x 32, K = 9 83.5 : 84.5; 40 x 16, K = 16 54.0 : 54.0;
+  //    80 x 16, K = 9 60.0 : 58.9; 56 x 16, K = 16 60.2 : 58.7; 256 x 16, K = 16
+  //    173 : 151.  Against the copy on the side the launch has to be earned back:
+  //    1 x 16, K = 9 41.6 : 38.9; 1 x 24 43.4 : 43.3; 1 x 32, K = 16 51 : 52; 1 x
+  //    64, K = 16 78 : 84.  Without the tables 64 x 16, K = 8 89 : 79.
   //  - multi-wave scan, up to 16 keys (a few vectors a candidate to load, like
   //    the single-wave one): 8 x 32, K = 8, d_state 320 90 : 96; 64 x 16, K = 4,
   //    320 72 : 73; 64 x 16, K = 8, 320 80 : 77; 16 x 16, K = 16, 512 90 : 90; 256
@@ -1985,7 +1988,7 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
   const int64_t bk = static_cast<int64_t>(B) * K;
   const bool beside = n_vec <= 4096;
   bool gate;
-  if (pc) gate = tab && !scan_gathers && (K > 8 ? bk <= 900 : bk <= 370 && !beside);
+  if (pc) gate = tab && !scan_gathers && (K > 8 ? bk <= 700 && !(beside && L <= 24) : bk <= 370 && !beside);
   else if (K <= 16) gate = tab && !beside && bk * static_cast<int64_t>(vsz) <= 80 << 10;
   else gate = tab || bk * static_cast<int64_t>(vsz) < 4 << 20;
   const bool fill_here = finish && tab && !scan_gathers && !gate && beside;

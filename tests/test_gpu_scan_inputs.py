@@ -20,6 +20,7 @@ brisk = pytest.importorskip("paper_2609_33390_amd")
     (64, 3, 8, 32, True), (2, 9, 9, 256, True), (56, 4, 16, 32, True), (57, 4, 16, 32, True), (3, 70, 16, 40, True),
     (3, 12, 24, 96, True), (3, 12, 24, 96, False), (2, 33, 64, 32, True), (4, 7, 6, 320, True), (4, 7, 6, 320, False),
     (5, 20, 16, 72, False), (2, 5, 4, 8, True), (1, 1, 12, 256, True),
+    (1, 24, 9, 32, True), (1, 25, 9, 32, True), (43, 4, 16, 32, True), (44, 4, 16, 32, True),
     (3, 5, 8, 257, True), (3, 5, 8, 257, False), (8, 24, 8, 257, True), (8, 24, 8, 320, True), (64, 3, 8, 320, True),
     (64, 3, 8, 257, True), (16, 6, 16, 512, True), (20, 5, 16, 512, True), (3, 6, 16, 512, False),
     (256, 2, 63, 256, False), (256, 2, 64, 256, False), (256, 2, 64, 256, True), (128, 2, 64, 511, False),
