@@ -763,9 +763,12 @@ __global__ __launch_bounds__(64 * TP_NW) __attribute__((amdgpu_waves_per_eu(2, 2
       const int g = tl * nk + kt;
       // slice g has landed, and every wave is done reading slice g - 1.  The
       // last slices have fewer younger copies, and the first of a tile has the
-      // stores of the tile before among them: they wait for all.
+      // stores of the tile before among them: they wait for all.  (From the
+      // second on the stores are done and only the copies of slice g + 1 are
+      // younger.)
       constexpr int kYounger = (TP_STAGES - 2) * TP_NDMA;
-      if (g + TP_STAGES - 2 < n_tiles * nk && (kt >= TP_STAGES - 1 || tl == 0))
+      static_assert(TP_STAGES == 3, "one younger slice");
+      if (g + TP_STAGES - 2 < n_tiles * nk && (kt > 0 || tl == 0))
         __builtin_amdgcn_s_waitcnt((kYounger & 15) | (((kYounger >> 4) & 3) << 14) | (7 << 4) | (0 << 8));
       else
         __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0 << 8));
