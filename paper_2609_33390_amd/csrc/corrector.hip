@@ -681,11 +681,10 @@ constexpr int TP_CPR = TP_BK / 8;                             // 16-byte chunks 
 constexpr int TP_STAGE = (TP_BN + TP_BJ) * TP_BK * 2;         // bytes
 constexpr int TP_NDMA = (TP_BN + TP_BJ) / 8 / TP_NW;          // copies per wave and slice, 8 rows each
 static_assert(TP_STAGES * TP_STAGE <= 160 * 1024, "LDS");
-// Cache policy of the token copies: non-temporal, so that the stream, which is
-// read once, does not push the weights out of L2 (482 against 415 us).
-constexpr int kStreamAux = 2;
-
 // One workgroup per compute unit (its LDS): two waves per SIMD.
+// STREAM: the token copies are non-temporal, so that the stream, which is read
+// once, does not push the weights out of L2 (482 against 415 us).
+template <bool STREAM>
 __global__ __launch_bounds__(64 * TP_NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void table_proj_kernel(
     TableProjJobs jobs) {
   __shared__ __align__(16) unsigned char smem[TP_STAGES * TP_STAGE];
@@ -736,7 +735,7 @@ __global__ __launch_bounds__(64 * TP_NW) __attribute__((amdgpu_waves_per_eu(2, 2
       const int q = i * TP_NW + wave;  // 8 staged rows a copy: tokens, then outputs
       if (q * 8 < TP_BN)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rt, (__attribute__((address_space(3))) void*)(base + q * 1024), 16,
-                                                 lane_voff + static_cast<unsigned>(q * 8) * row_bytes + k0b, 0, 0, kStreamAux);
+                                                 lane_voff + static_cast<unsigned>(q * 8) * row_bytes + k0b, 0, 0, STREAM ? 2 : 0);
       else
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rp, (__attribute__((address_space(3))) void*)(base + q * 1024), 16,
                                                  lane_voff + static_cast<unsigned>(q * 8 - TP_BN) * row_bytes + k0b, 0, 0, 0);
@@ -845,6 +844,10 @@ struct TableLiftJobs {
 };
 constexpr int TL_NW = 8, TL_BN = 16 * TL_NW, TL_BJ = 64;
 
+// Stores are non-temporal beyond two steps: 126464 tokens, 256 out, 128 in 187 ->
+// 162 us.  With fewer the kernel waits for them alone, and for plain ones less
+// (50000 tokens x 768, the whole preparation with 64 in and 128 out 102 : 88 us,
+// with 128 in and 256 out 115 : 113, with 256 in and 512 out 354 : 369).
 template <int NK>
 __global__ __launch_bounds__(64 * TL_NW) void table_lift_kernel(TableLiftJobs jobs) {
   constexpr int KC = NK * 32, ROW = KC + 8;  // staged matrix row: KC columns, padded against bank conflicts
@@ -970,7 +973,9 @@ __global__ __launch_bounds__(64 * TL_NW) void table_lift_kernel(TableLiftJobs jo
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[a][q] = j + q < ds ? acc[a][q] : 0.f;
         if ((vs & 3) == 0) {
-          if (j < vs) __builtin_nontemporal_store(acc[a], reinterpret_cast<floatx4*>(o + j));
+          if (j >= vs) continue;
+          if constexpr (NK > 2) __builtin_nontemporal_store(acc[a], reinterpret_cast<floatx4*>(o + j));
+          else *reinterpret_cast<floatx4*>(o + j) = acc[a];
         } else {
 #pragma unroll
           for (int q = 0; q < 4; ++q)
@@ -2140,7 +2145,17 @@ void launch_corrector_prepare(const brisk_corrector& c, const uint16_t* lm_head,
   pj.job[0] = TableProjJob{tok_embed, c.P_e, PE, V, c.d_tproj};
   pj.job[1] = TableProjJob{lm_head, c.W_c, PC, V, c.rank};
   const int jt = (std::max(c.d_tproj, c.rank) + TP_BJ - 1) / TP_BJ;
-  hipLaunchKernelGGL(table_proj_kernel, dim3(256, jt), dim3(64 * TP_NW), 0, s, pj);
+  // The tokens' rows are read non-temporally unless they share 128-byte lines or
+  // both embeddings fit the 256 MiB last-level cache, where the next preparation
+  // finds them (the whole preparation, not / non-temporal: 50000 x 1000, d_state
+  // 64 101 : 124 us; 126464 x 1032, 128 292 : 328; 20000 x 2048, 64 58 : 64; 50000
+  // x 768, 256 111 : 115; 75000 x 2048, 256 276 : 250; 126464 x 4096, 256 609 :
+  // 554).
+  const bool lines = d % 64 == 0 && ((reinterpret_cast<uintptr_t>(lm_head) | reinterpret_cast<uintptr_t>(tok_embed)) & 127u) == 0;
+  if (lines && static_cast<size_t>(V) * d * 4 > (size_t{256} << 20))
+    hipLaunchKernelGGL(table_proj_kernel<true>, dim3(256, jt), dim3(64 * TP_NW), 0, s, pj);
+  else
+    hipLaunchKernelGGL(table_proj_kernel<false>, dim3(256, jt), dim3(64 * TP_NW), 0, s, pj);
 
   // runs of 8 along c (rows of W_z and W_h) or along j (rows of W_s)
   auto mat = [&](const uint16_t* m, int m_rs, int m_cs, int C, float* out) {
@@ -2149,14 +2164,15 @@ void launch_corrector_prepare(const brisk_corrector& c, const uint16_t* lm_head,
     return TableLiftMat{m, m_rs, m_cs, vec, out};
   };
   const size_t tstride = static_cast<size_t>(V) * vsz;
+  const uint16_t* maps[3] = {c.W_s, c.W_z + tp_off, c.W_h + tp_off};
   TableLiftJobs lj{};
   lj.n = V;
   lj.ds = ds;
   lj.vs = static_cast<int>(vsz);
-  lj.job[0] = TableLiftJob{PC, c.rank, 1, {mat(c.W_s, 1, ds, c.rank, tables), {}}};
+  lj.job[0] = TableLiftJob{PC, c.rank, 1, {mat(maps[0], 1, ds, c.rank, tables), {}}};
   lj.job[1] = TableLiftJob{PE, c.d_tproj, 2,
-                           {mat(c.W_z + tp_off, d_in, 1, c.d_tproj, tables + tstride),
-                            mat(c.W_h + tp_off, d_in, 1, c.d_tproj, tables + 2 * tstride)}};
+                           {mat(maps[1], d_in, 1, c.d_tproj, tables + tstride),
+                            mat(maps[2], d_in, 1, c.d_tproj, tables + 2 * tstride)}};
   const int cmax = std::max(c.d_tproj, c.rank);
   const dim3 grid((V + TL_BN - 1) / TL_BN, 2), blk(64 * TL_NW);
   if (cmax <= 64) hipLaunchKernelGGL(table_lift_kernel<2>, grid, blk, 0, s, lj);

@@ -17,6 +17,7 @@ DEV = "cuda"
     (5, 8, 4, 3, 1, 1), (16, 64, 32, 16, 16, 16), (777, 200, 96, 48, 48, 48), (2049, 136, 250, 30, 31, 33),
     (4096, 192, 256, 128, 128, 128), (33000, 72, 64, 32, 64, 65), (700, 128, 320, 100, 130, 200),
     (1000, 264, 512, 256, 256, 256), (501, 64, 257, 64, 2, 129), (32768 + 17, 128, 16, 8, 96, 100),
+    (40000, 64, 256, 128, 128, 128), (70000, 1024, 32, 16, 16, 16), (70000, 1032, 32, 16, 16, 65),
 ])
 def test_tables_match_their_definition(V, d, ds, dh, dt, rank):
     g = torch.Generator().manual_seed(V + d)
@@ -35,10 +36,11 @@ def test_tables_match_their_definition(V, d, ds, dh, dt, rank):
         assert err < 2e-6, (k, float(err))
 
 
-def test_table_padding_is_zero_beside_infinite_inputs():
+@pytest.mark.parametrize("V", [600, 16400])
+def test_table_padding_is_zero_beside_infinite_inputs(V):
     """Weights and embeddings with infinities stay in their own tokens and
     outputs; the padding past d_state stays zero."""
-    V, d, ds = 600, 72, 40
+    d, ds = 72, 40
     g = torch.Generator().manual_seed(3)
     dims = dict(d_state=ds, d_hproj=8, d_tproj=24, d_pos=3, d_feat=5, rank=24, max_L=4)
     psi = {n: (torch.randn(s, generator=g) * 0.1).to(torch.bfloat16) for n, s in synth.psi_shapes(dims, d).items()}
