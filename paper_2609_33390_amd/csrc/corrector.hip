@@ -827,6 +827,8 @@ __global__ __launch_bounds__(64 * TP_NW) __attribute__((amdgpu_waves_per_eu(2, 2
 // input is read and split once; lift's 64 x 64 tiles do both four times per
 // matrix.  At 126464 tokens, 128 columns in and 256 out: 234 us as lift, 171-187
 // here, 162 with non-temporal stores (517 MB of inputs and tables, 3.2 TB/s).
+// A workgroup walks its columns one tile after the other, so it takes many
+// tokens to fill the chip (see launch_corrector_prepare).
 struct TableLiftMat {
   const uint16_t* m;  // M(j, c) = m[j * m_rs + c * m_cs]
   int m_rs, m_cs;
@@ -2145,17 +2147,35 @@ void launch_corrector_prepare(const brisk_corrector& c, const uint16_t* lm_head,
   pj.job[0] = TableProjJob{tok_embed, c.P_e, PE, V, c.d_tproj};
   pj.job[1] = TableProjJob{lm_head, c.W_c, PC, V, c.rank};
   const int jt = (std::max(c.d_tproj, c.rank) + TP_BJ - 1) / TP_BJ;
+  // Small vocabularies take the kernels of the rerank: table_proj has 128 shares
+  // a matrix and a 256-token tile in each, so at 16000 tokens half of a tile is
+  // rows that do not exist, and table_lift has a workgroup per 128 tokens, which
+  // leaves compute units idle and walks its columns one tile after the other.
+  // The whole preparation, table kernels : rerank's, d = 768, d_state 64, 256 and
+  // 512, in us: 1000 tokens 31 : 17, 43 : 19, 99 : 25; 8000 33 : 24, 47 : 34, 109
+  // : 77; 12000 34 : 31, 47 : 43, 112 : 105; 16000 34 : 34, 49 : 51, 118 : 135;
+  // 20000 39 : 45, 60 : 65, 171 : 176; 50000 86 : 103, 115 : 160, 359 : 429.
   // The tokens' rows are read non-temporally unless they share 128-byte lines or
   // both embeddings fit the 256 MiB last-level cache, where the next preparation
   // finds them (the whole preparation, not / non-temporal: 50000 x 1000, d_state
   // 64 101 : 124 us; 126464 x 1032, 128 292 : 328; 20000 x 2048, 64 58 : 64; 50000
   // x 768, 256 111 : 115; 75000 x 2048, 256 276 : 250; 126464 x 4096, 256 609 :
   // 554).
-  const bool lines = d % 64 == 0 && ((reinterpret_cast<uintptr_t>(lm_head) | reinterpret_cast<uintptr_t>(tok_embed)) & 127u) == 0;
-  if (lines && static_cast<size_t>(V) * d * 4 > (size_t{256} << 20))
-    hipLaunchKernelGGL(table_proj_kernel<true>, dim3(256, jt), dim3(64 * TP_NW), 0, s, pj);
-  else
-    hipLaunchKernelGGL(table_proj_kernel<false>, dim3(256, jt), dim3(64 * TP_NW), 0, s, pj);
+  if (V >= 16000) {
+    const bool lines = d % 64 == 0 && ((reinterpret_cast<uintptr_t>(lm_head) | reinterpret_cast<uintptr_t>(tok_embed)) & 127u) == 0;
+    if (lines && static_cast<size_t>(V) * d * 4 > (size_t{256} << 20))
+      hipLaunchKernelGGL(table_proj_kernel<true>, dim3(256, jt), dim3(64 * TP_NW), 0, s, pj);
+    else
+      hipLaunchKernelGGL(table_proj_kernel<false>, dim3(256, jt), dim3(64 * TP_NW), 0, s, pj);
+  } else {
+    ProjJobs gj{};
+    gj.d = d;
+    gj.splits = 1;
+    gj.job[0] = ProjJob{tok_embed, nullptr, V, c.d_tproj, V, c.P_e, PE, static_cast<size_t>(V) * c.d_tproj};
+    gj.job[1] = ProjJob{lm_head, nullptr, V, c.rank, V, c.W_c, PC, static_cast<size_t>(V) * c.rank};
+    const int gx = std::max(proj_tiles(V, c.d_tproj, 128), proj_tiles(V, c.rank, 128));
+    hipLaunchKernelGGL(gather_proj_kernel<128>, dim3(gx, 2, 1), dim3(256), 0, s, gj);
+  }
 
   // runs of 8 along c (rows of W_z and W_h) or along j (rows of W_s)
   auto mat = [&](const uint16_t* m, int m_rs, int m_cs, int C, float* out) {
@@ -2165,6 +2185,28 @@ void launch_corrector_prepare(const brisk_corrector& c, const uint16_t* lm_head,
   };
   const size_t tstride = static_cast<size_t>(V) * vsz;
   const uint16_t* maps[3] = {c.W_s, c.W_z + tp_off, c.W_h + tp_off};
+  // Where lift cannot read its inputs and matrices as vectors, table_lift wins
+  // earlier (d = 1000, d_state 200: 8000 tokens 54 : 50, 12000 59 : 67, 16000 62 :
+  // 80 us).
+  bool vectors = c.rank % 16 == 0 && c.d_tproj % 16 == 0 && ds % 16 == 0 && d_in % 8 == 0;
+  for (const uint16_t* m : maps) vectors = vectors && (reinterpret_cast<uintptr_t>(m) & 15u) == 0;
+  if (V < (vectors ? 16000 : 10000)) {
+    auto fterm = [&](const float* in, int C, const uint16_t* m, int m_rs, int m_cs) {
+      const bool a16 = (reinterpret_cast<uintptr_t>(in) & 15u) == 0 && C % 16 == 0;
+      const bool m16 = (reinterpret_cast<uintptr_t>(m) & 15u) == 0 &&
+                       (m_cs == 1 ? m_rs % 8 == 0 && C % 16 == 0 : m_rs == 1 && m_cs % 8 == 0 && ds % 16 == 0);
+      return LiftTerm{in, 0, C, 1, 0, C, m, m_rs, m_cs, a16 ? 1 : 0, m16 ? 1 : 0};
+    };
+    const LiftTerm none{nullptr, 0, 0, 0, 0, 0, nullptr, 0, 0, 0, 0};
+    LiftJobs gj{};
+    gj.ds = ds;
+    gj.job[0] = LiftJob{{fterm(PC, c.rank, maps[0], 1, ds), none}, V, tables, 1, vsz, vsz};
+    gj.job[1] = LiftJob{{fterm(PE, c.d_tproj, maps[1], d_in, 1), none}, V, tables + tstride, 1, vsz, vsz};
+    gj.job[2] = LiftJob{{fterm(PE, c.d_tproj, maps[2], d_in, 1), none}, V, tables + 2 * tstride, 1, vsz, vsz};
+    const dim3 grid((V + LT_BN - 1) / LT_BN, static_cast<int>((vsz + LT_BJ - 1) / LT_BJ), 3);
+    hipLaunchKernelGGL(lift_kernel<1>, grid, dim3(256), 0, s, gj);
+    return;
+  }
   TableLiftJobs lj{};
   lj.n = V;
   lj.ds = ds;

@@ -1,7 +1,8 @@
 """GPU parity of the per-token tables (brisk_corrector_prepare) with their
 definition in float64, at the edges of the kernels that build them: token
 counts either side of a share's 16-token cut and of a 256-token tile, widths
-that are not multiples of 8 or 4, one to eight 32-wide steps, a ragged d."""
+that are not multiples of 8 or 4, one to eight 32-wide steps, a ragged d,
+vocabularies on both sides of the kernels' rules."""
 import pytest
 import torch
 
@@ -17,7 +18,11 @@ DEV = "cuda"
     (5, 8, 4, 3, 1, 1), (16, 64, 32, 16, 16, 16), (777, 200, 96, 48, 48, 48), (2049, 136, 250, 30, 31, 33),
     (4096, 192, 256, 128, 128, 128), (33000, 72, 64, 32, 64, 65), (700, 128, 320, 100, 130, 200),
     (1000, 264, 512, 256, 256, 256), (501, 64, 257, 64, 2, 129), (32768 + 17, 128, 16, 8, 96, 100),
-    (40000, 64, 256, 128, 128, 128), (70000, 1024, 32, 16, 16, 16), (70000, 1032, 32, 16, 16, 65),
+    (9999, 72, 40, 8, 24, 100), (10000, 72, 40, 8, 24, 100), (15999, 200, 64, 32, 64, 64), (16000, 200, 64, 32, 64, 64),
+    (15999, 64, 320, 160, 160, 176), (16000, 64, 320, 160, 160, 176), (16001, 128, 512, 256, 256, 240),
+    (16016, 64, 250, 30, 193, 192), (70000, 1024, 32, 16, 16, 16), (70000, 1032, 32, 16, 16, 65),
+    (16005, 8, 4, 3, 1, 1), (16005, 136, 250, 30, 31, 33), (16384, 64, 32, 16, 16, 16), (32768, 192, 96, 48, 48, 48),
+    (16005, 128, 320, 100, 130, 200), (16005, 72, 257, 64, 2, 129), (40000, 64, 256, 128, 128, 128),
 ])
 def test_tables_match_their_definition(V, d, ds, dh, dt, rank):
     g = torch.Generator().manual_seed(V + d)
