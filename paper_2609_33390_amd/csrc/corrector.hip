@@ -251,7 +251,9 @@ __global__ __launch_bounds__(256) void gather_proj_kernel(ProjJobs jobs) {
     else cross_dots<8, 2>(jobs.cross, d);
     return;
   }
-  if (blockIdx.y == kMaxProjJobs + 1) {
+  // (only unsplit batches take the wide tiles, and they have no rows to copy on
+  // the side; code for it here cost 256 x 16, K = 8 2 us of 55)
+  if (BJ == 64 && blockIdx.y == kMaxProjJobs + 1) {
     fill_rows(jobs.fill, (blockIdx.z * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6), gridDim.x * gridDim.z * 4);
     return;
   }
@@ -1996,7 +1998,7 @@ void launch_rerank(const brisk_corrector& c, const uint16_t* hidden, const uint1
   //    : 2895.
   const int n_vec = rows * 3 * K + 2 * B;
   const int64_t bk = static_cast<int64_t>(B) * K;
-  const bool beside = n_vec <= 4096;
+  const bool beside = n_vec <= 4096 && bj == 64;
   bool gate;
   if (pc) gate = tab && !scan_gathers && (K > 8 ? bk <= 700 && !(beside && L <= 24) : bk <= 370 && !beside);
   else if (K <= 16) gate = tab && !beside && bk * static_cast<int64_t>(vsz) <= 80 << 10;
