@@ -13,6 +13,7 @@ import oracle
 import synth
 from oracle_io import oracle_inputs
 from parity import SCORE_TOL, check_candidates, check_gpu_order, check_rerank, rerank_pick_ok
+from plan import plan
 
 pytestmark = pytest.mark.gpu
 
@@ -303,15 +304,17 @@ def test_propose_monotone_logits(order, K):
     check_candidates(cl.cpu().numpy(), ci.cpu().numpy(), ol)
 
 
-@pytest.mark.parametrize("K", [8, 16])
-def test_propose_tied_groups_overflow(K):
-    # 300 rows (a second row tile of 44 rows and 212 padding positions) over
-    # three vocabulary tiles per workgroup.  In the first third of the
-    # vocabulary every run of 64 tokens shares one lm_head row, so a tile's
-    # logits tie in blocks of 64: a whole block reaches any bound, more than
-    # a survivor queue holds, and those tiles take the full path; the rest of
-    # the vocabulary is spread normally and filtered.  Ties go to the lower id.
-    rows, d, V = 300, 64, (1 << 17) + 37
+@pytest.mark.parametrize("rows,K", [(300, 8), (300, 16), (500, 8), (500, 16)])
+def test_propose_tied_groups_overflow(rows, K):
+    # 300 rows run on three 128-row tiles (84 padding positions in the last)
+    # with seven vocabulary tiles per workgroup, 500 on two 256-row tiles (12)
+    # with five.  In the first third of the vocabulary every run of 64 tokens
+    # shares one lm_head row, so a tile's logits tie in blocks of 64: a whole
+    # block reaches any bound, more than a survivor queue holds, and those tiles
+    # take the full path; the rest of the vocabulary is spread normally and
+    # filtered.  Ties go to the lower id.
+    d, V = 64, (1 << 17) + 37
+    assert plan(rows, d, V, K)[0] == (128 if rows == 300 else 256)
     g = torch.Generator(device="cpu").manual_seed(43 + K)
     H = torch.randn(rows, d, generator=g).to(torch.bfloat16)
     W = torch.randn(V, d, generator=g) * 0.05

@@ -12,6 +12,7 @@ import torch
 import oracle
 import synth
 from parity import check_candidates
+from plan import plan
 
 pytestmark = pytest.mark.gpu
 
@@ -29,32 +30,49 @@ def test_row_tiles_and_partial_shares(rows, d, V, K):
     g = torch.Generator().manual_seed(rows * 7919 + V)
     H = torch.randn(rows, d, generator=g).to(torch.bfloat16)
     W = (torch.randn(V, d, generator=g) * 0.1).to(torch.bfloat16)
-    # the last token of the vocabulary is the top one of every third row
-    W[V - 1] = (H[::3].float().mean(0) * 3).to(torch.bfloat16)
+    # the last token of the vocabulary, in the last place of the last share, is
+    # the top one of the rows at the tiles' edges and of every 40th or so
+    ends = [r for t in (64, 128, 192, 256) for r in range(t - 1, rows, t)]
+    rs = np.array(sorted({0, rows - 1, *range(0, rows, max(1, rows // 40)), *ends}))
+    u = torch.randn(d, generator=g)
+    u /= u.norm()
+    H[rs] = (H[rs].float() + 8 * u).to(torch.bfloat16)
+    W[V - 1] = (4 * u).to(torch.bfloat16)
     print(f"rows {rows} d {d} V {V} K {K}", flush=True)
     cl, ci = brisk.propose_block(H.to(DEV), W.to(DEV), K)
     torch.cuda.synchronize()
-    ends = [r for t in (64, 128, 192, 256) for r in range(t - 1, rows, t)]
-    rs = np.array(sorted({0, rows - 1, *range(0, rows, max(1, rows // 40)), *ends}))
     ol = oracle.lm_logits(oracle.bf16_to_f64(synth.bf16_bits(H[rs])), synth.bf16_bits(W))
+    assert (ol.argmax(1) == V - 1).all()
     check_candidates(cl.cpu().numpy()[rs], ci.cpu().numpy()[rs], ol)
 
 
-def test_partial_tiles_keep_exact_ties_in_id_order():
-    """Equal LM-head rows in whole and partial tiles of different shares have
-    equal logits and come in id order."""
-    rows, d, V, K = 200, 192, 256 * 300, 16
+@pytest.mark.parametrize("rows,V,left", [(40, 256 * 300, 0), (128, 256 * 300 + 5, 0), (200, 256 * 301 - 7, 249), (512, 64 * 600 + 9, 9)])
+def test_partial_tiles_keep_exact_ties_in_id_order(rows, V, left):
+    """Equal LM-head rows in the partial tiles of different shares, and in whole
+    ones, have equal logits and come in id order.  Up to 128 rows these sizes
+    make 256 equal shares of a whole and a partial tile; above, the last tile
+    of the vocabulary holds `left` tokens."""
+    d, K = 192, 16
     g = torch.Generator().manual_seed(5)
+    if left:
+        assert V % 256 == left
+        ids = torch.cat([torch.arange(V - left, V)[:8], torch.randperm(V - 300, generator=g)[:K - 8]])
+    else:
+        assert plan(rows, d, V, K)[1] == 256
+        start = [(s * V // 256) & ~15 for s in range(256)] + [V]
+        shares = torch.randperm(255, generator=g)[:K - 3].tolist() + [255]
+        ids = torch.tensor([start[s] + 256 + (7 * s) % (start[s + 1] - start[s] - 256) for s in shares] + [0, 300])
+    ids = ids.unique()
+    assert len(ids) == K
     H = torch.randn(rows, d, generator=g).to(torch.bfloat16)
     W = (torch.randn(V, d, generator=g) * 0.01).to(torch.bfloat16)
-    ids = torch.randperm(V, generator=g)[:K].sort().values
-    W[ids] = (H.float().mean(0) * 2).to(torch.bfloat16)
+    W[ids] = (H[:200].float().mean(0) * 2).to(torch.bfloat16)
     cl, ci = brisk.propose_block(H.to(DEV), W.to(DEV), K)
     cl, ci = cl.cpu(), ci.cpu()
     # other logits have a standard deviation of 0.01 |H| ~ 0.14: the largest of
     # V is near 0.6, and 1.2 is out of their reach
     top = H.float() @ W[ids[0]].float() > 1.2
-    assert int(top.sum()) > 10
+    assert int(top.sum()) > 5
     assert torch.equal(ci[top], ids.to(torch.int32).expand(int(top.sum()), K))
     assert torch.equal(cl[top], cl[top][:, :1].expand(-1, K))
 

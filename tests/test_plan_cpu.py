@@ -1,19 +1,9 @@
 """Host-side checks of what the LM-head pass runs on: no GPU needed."""
-import ctypes
-
 import pytest
 
-import paper_2609_33390_amd as brisk
+from plan import plan
 
 CUS = 256
-
-
-def _plan(rows, d, V, K):
-    """Rows of a row tile, workgroups, non-temporal lm_head copies."""
-    fn = getattr(brisk.lib(), "_ZN5brisk17propose_plan_infoEiiiiPi")   # internal, not part of the C ABI
-    out = (ctypes.c_int * 3)()
-    fn(rows, d, V, K, out)
-    return list(out)
 
 
 @pytest.mark.parametrize("V", [20000, 126464, 152064])
@@ -21,7 +11,7 @@ def _plan(rows, d, V, K):
 def test_many_rows_take_the_fewest_rounds(rows, V):
     """Where a row tile's share is the whole vocabulary, the tile with the
     fewest rounds of workgroups."""
-    tile, wgs, _ = _plan(rows, 8, V, 8)
+    tile, wgs, _ = plan(rows, 8, V, 8)
     assert wgs == -(-rows // tile)
     assert -(-wgs // CUS) == -(-rows // (256 * CUS))
 
@@ -33,7 +23,7 @@ def test_many_rows_take_the_fewest_rounds(rows, V):
 ])
 def test_only_an_lm_head_beyond_the_last_level_cache_is_streamed(rows, d, V, want):
     """Non-temporal copies: one row tile, rows of whole lines, over 256 MiB."""
-    assert _plan(rows, d, V, 8)[2] == want
+    assert plan(rows, d, V, 8)[2] == want
 
 
 @pytest.mark.parametrize("rows", [33, 64, 65, 128])
@@ -42,5 +32,5 @@ def test_shares_hold_a_whole_tile(rows):
     below 256 shares of one tile (cut at multiples of 16) every share but the
     last is a run of whole tiles."""
     for V in (20000, 32768, 33000, 50000, 65536, 69631):
-        assert _plan(rows, 2048, V, 8)[1] <= -(-V // 256), V
-    assert _plan(rows, 2048, 69632, 8)[1] == CUS
+        assert plan(rows, 2048, V, 8)[1] <= -(-V // 256), V
+    assert plan(rows, 2048, 69632, 8)[1] == CUS
