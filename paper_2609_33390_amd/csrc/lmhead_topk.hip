@@ -288,9 +288,9 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
   // position's KP-th largest logit: the KP-th of the position's two lists,
   // raised on the first two tiles by a seed from the tile itself) and
   // queues only the survivors, which the
-  // position's list owners then fold.  A tile whose queues overflow, and a
-  // first tile that is not whole, take the full path.  Lists of up to 16
-  // keys; longer lists keep the full path on every tile.
+  // position's list owners then fold.  A tile whose queues overflow, and the
+  // only tile of a vocabulary smaller than one, take the full path.  Lists of
+  // up to 16 keys; longer lists keep the full path on every tile.
   constexpr bool kFilt = !SAMPLE && C::WAVES_R == 2 && C::EPI_ALIAS && KP <= kFiltKeys;
   constexpr bool kSeed = kFilt;
   float* const s_pthr = reinterpret_cast<float*>(smem + C::POS_OFF);        // [BR]
@@ -316,12 +316,12 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
     vb = group * tiles_per_group * C::BV;
     ve = min(V, vb + tiles_per_group * C::BV);
   }
-  // A share shorter than a tile (the last one, at 256-row tiles and V just past
-  // a whole number of them) would have to fold every logit: it has no whole
-  // tile to seed a threshold from.  Its tile starts early instead, at the rows
-  // of the share before, which bound the row's KP-th logit as well as its own
-  // and are dropped when the lists take them.  33000 tokens x 1024, 250 rows, 16
-  // keys: 119 -> 63 us.  (V below one tile stays as it is.)
+  // A share shorter than a tile (the last one, where V is just past a whole
+  // number of tiles) would have to fold every logit: it has no whole tile to
+  // seed a threshold from.  Its tile starts early instead, at the rows of the
+  // share before, which bound the row's KP-th logit as well as its own and are
+  // dropped when the lists take them.  33000 tokens x 1024, 250 rows, 16 keys:
+  // 119 -> 63 us.  (V below one tile stays as it is.)
   const int vlo = vb;
   if constexpr (kFilt) {
     if (ve - vb < C::BV) vb = max(0, ve - C::BV);
@@ -581,9 +581,10 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
       // phase.  The second group starts one phase late and the first waits
       // one out at the end, so both pass the same barriers.  In lockstep both
       // waves of a SIMD wait on LDS together and then contend for the matrix
-      // cores: 3347 against 3240 us at 4096 rows x 126464 tokens (d = 4096),
-      // 500 against 476 us at 512.  Raising the priority of the multiplying
-      // wave made no difference, nor did spreading the copies over the phases.
+      // cores: 3347 against 3240 us at 4096 rows x 126464 tokens (d = 4096) on
+      // one card, 500 against 476 us at 512; over several cards the 4096-row
+      // call gained 1 to 4%.  Raising the priority of the multiplying wave made
+      // no difference, nor did spreading the copies over the phases.
       //
       // Phase p of slice g is 4g + p, one more for the second group.  Its
       // first phase refills the buffer of slice g - 1, which the other group
@@ -858,7 +859,7 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
     }
     // Large-row tile: one copy of the consume loop, run once per accumulator
     // block (its LDS store keeps static register indices); on this tile the
-    // path runs after an overflow, on a first tile that is not whole and for
+    // path runs after an overflow, on a vocabulary smaller than a tile and for
     // lists longer than 16 keys, and unrolling it per block made the kernel
     // several times larger.  Smaller tiles unroll it.
     constexpr bool kOneConsume = C::BR >= 128;
