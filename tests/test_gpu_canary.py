@@ -50,8 +50,8 @@ SHAPES = [  # name, B, L, d, V, K
 ]
 
 
-def _block(B, L, d, V, K, seed):
-    wl = synth.Workload("canary", B=B, L=L, d=d, V=V, K=K, r=32, sigma=0.3, flat_frac=0.5, seed=seed)
+def _block(B, L, d, V, K, seed, r=32):
+    wl = synth.Workload("canary", B=B, L=L, d=d, V=V, K=K, r=r, sigma=0.3, flat_frac=0.5, seed=seed)
     return wl, synth.make_block(wl, DEV)
 
 
@@ -100,8 +100,24 @@ def test_tables_split_and_noalloc_entry_points_stay_in_bounds(name, B, L, d, V, 
     the rerank that reads them (on the 70-sequence shape the scan gathers the
     table rows itself; with 64 keys the multi-wave scan runs) and the rerank
     split at the candidates, each into guarded buffers."""
-    print(f"[canary] tables, split and no-alloc entries: {name} B={B} L={L} d={d} V={V} K={K}", flush=True)
-    wl, blk = _block(B, L, d, V, K, 13)
+    _tables_split_and_noalloc(name, B, L, d, V, K, 32)
+
+
+@pytest.mark.parametrize("name,B,L,d,V,K,r", [
+    ("table-kernels-short-share", 2, 25, 64, 33001, 12, 64),    # 50 rows: the last share of the vocabulary is 233 tokens
+    ("table-kernels-odd-state", 3, 5, 72, 16003, 8, 257), ("long-state-gate", 8, 24, 72, 16500, 8, 320),
+    ("long-state-copies", 64, 3, 72, 700, 8, 320), ("long-state-k64", 4, 6, 64, 20011, 64, 512),
+    ("copies-k16", 44, 4, 64, 700, 16, 32),
+])
+def test_tables_split_and_noalloc_stay_in_bounds_on_every_route(name, B, L, d, V, K, r):
+    """The same entry points on the other routes of the table build, of the
+    copies of table rows and of the gate pass."""
+    _tables_split_and_noalloc(name, B, L, d, V, K, r)
+
+
+def _tables_split_and_noalloc(name, B, L, d, V, K, r):
+    print(f"[canary] tables, split and no-alloc entries: {name} B={B} L={L} d={d} V={V} K={K} r={r}", flush=True)
+    wl, blk = _block(B, L, d, V, K, 13, r)
     rows = B * L
     L_ = brisk.lib()
     cl, ci = Guarded((rows, K), torch.float32), Guarded((rows, K), torch.int32)
