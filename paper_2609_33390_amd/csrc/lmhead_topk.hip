@@ -756,12 +756,17 @@ __global__ __launch_bounds__(C::NTA) __attribute__((amdgpu_waves_per_eu(C::NTA /
 #pragma unroll
           for (int y = 0; y < C::TR; ++y) {
             float t1 = -INFINITY, t2 = -INFINITY;
+            // The median of the two and a logit is the new second; of a NaN and
+            // t2 <= t1 it is the smaller, t2.  (The start is hidden from the
+            // compiler, which would fold a median with -inf into a minimum, and
+            // that returns t1.)
+            if constexpr (M == 2) asm("" : "+v"(t1), "+v"(t2));
 #pragma unroll
             for (int x = 0; x < C::TV; ++x)
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
                 const float v = acc[x][y][q];
-                if constexpr (M == 2) t2 = v > t1 ? t1 : fmaxf(t2, v);  // a NaN leaves both as they are
+                if constexpr (M == 2) t2 = __builtin_amdgcn_fmed3f(t1, t2, v);
                 t1 = fmaxf(t1, v);
               }
             const int p = wr * C::WR + y * 16 + l15;
